@@ -28,6 +28,11 @@ COMMON = [
     "-I" + INCLUDE, "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
 ]
 
+# A wave of the biased kernel holds its rows in arrays that unrolling turns into
+# registers.  Promoted to vectors before that, the FP32 arrays are copied whole
+# at every row guard: 253 VGPRs and 218 AGPRs instead of 70 and 0.
+EXTRA = {"cfd_biased.hip": ["-mllvm", "-disable-promote-alloca-to-vector=1"]}
+
 
 def hipcc() -> str:
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")):
@@ -39,7 +44,7 @@ def hipcc() -> str:
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    cmd = [hipcc()] + COMMON + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [hipcc()] + COMMON + EXTRA.get(src, []) + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -18,28 +18,34 @@
 // the grid): c d f = min(c, 0) D[right] f + max(c, 0) D[left] f.
 //
 // W schemes (Tab. ccuw_deg_one_col) add w2 s_k to every interior row's right
-// side (-w2 s_k for the right bias), s the embedded second derivative another
-// launch left in the plan scratch and w2 = a2 h^2; the closure rows take none.
+// side (-w2 s_k for the right bias), s the embedded second derivative of unit
+// spacing and w2 = a2; the closure rows take none.
 // U schemes (Tab. ucd_slow) read s, the sampled f'', from an input field and
 // add it on every row, the closure row with its own weight w2c.
 //
-// Partitioned kernel (lines of up to 64 nodes): one lane per line, 64 lines
-// per wave; a line is cut into P = 1, 2 or 4 partitions of at most L = 8, 12
-// or 16 rows (the fewest partitions with at most 12 rows where possible),
-// one wave each, so a workgroup of four waves holds 4 / P groups of 64
-// lines.  A wave issues every load of its partition (its rows and the
-// stencil halo) before any arithmetic and keeps them in registers.  Each
-// bias is solved locally with a zero value entering the partition (the
-// closure rows where the partition holds them); the exact solution is the
-// local one plus (-alpha)^distance times the true value entering it.  The
-// waves exchange their local end values through LDS and each walks the
-// chain of partitions before it (around the line on periodic lines, closed
-// by 1 / (1 - (-alpha)^N)) to get its entering values.  Lanes run along the
-// contiguous direction of the block for y and z lines, so each load and
-// store of a wave is one coalesced access; x lines are staged through an LDS
-// tile filled and drained with contiguous accesses along the rows.
+// Wave kernel (x lines of up to 1024 nodes, y and z lines of up to 256): a
+// wave owns 64 / P lines of one field, P = 1 .. 64 a power of two, and its
+// lanes are the P partitions of those lines (lane = partition * (64 / P) +
+// line, at most 8, 12 or 16 rows each).  A lane issues every load of its rows
+// and their stencil halo before any arithmetic and keeps them in registers.
+// Each bias is solved locally with a zero value entering the partition (the
+// closure rows where the lane holds them); the exact solution is the local one
+// plus (-alpha)^distance times the true value entering it, which a scan over
+// the partitions' local end values with the constant weight (-alpha)^rows
+// gives by lane shuffles (around the line on periodic lines, closed by
+// 1 / (1 - (-alpha)^N)).  Consecutive lines of y and z are consecutive x, so
+// their accesses run along the contiguous direction; x lines are staged
+// through a piece of LDS that only this wave uses, filled and drained with
+// contiguous accesses.  So a wave never waits for another: there is no
+// workgroup barrier, and the phases of one wave (loads, solve, stores) overlap
+// the others'.  One launch takes every direction and length of a plan's
+// operators with one stencil class.
 //
-// Sweep kernel (longer lines): one lane per line, a register window of
+// W schemes solve their embedded second derivative in the same registers: its
+// constant-coefficient tridiagonal system splits into a forward and a backward
+// bidiagonal recurrence of the same form.
+//
+// Sweep kernel (longer y and z lines): one lane per line, a register window of
 // 2 HB + 3 samples slid one node per row; the right-biased sweep leaves
 // min(c,0) D[right] f in the output, the left-biased sweep adds the rest.
 #include <hip/hip_runtime.h>
@@ -113,250 +119,510 @@ __device__ __forceinline__ void load_coef(BCoef<T, HB> &q, const T *rec) {
     for (int m = -HB; m <= HB + 1; ++m) q.c[m + HB] = rec[12 + kBiasHalf + m];
 }
 
-// Walk of a thread over the elements e = threadIdx.x, + 256, ... of a
-// [lines][cols] tile (cols <= 256) in row-major order, with the (u, v) position of its line
-// kept up to date, so the fill and drain loops divide only once.
-struct TileWalk {
-    int l, j, dq, dr, cols;   // row (line of the workgroup), column, row / column step
-    int ln, uu, vv;           // line index in the pass, its u and v
-    __device__ __forceinline__ TileWalk(int t, int cols_, int line0, int nu) : cols(cols_) {
-        l = t / cols;
-        j = t - l * cols;
-        dq = 256 / cols;
-        dr = 256 - dq * cols;
-        ln = line0 + l;
-        uu = ln % nu;
-        vv = ln / nu;
+// Orders the LDS accesses of one wave (its LDS operations execute in order, so
+// only the compiler has to keep them so); no other wave shares the tile.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Walk of a lane over the elements e = lane, lane + 64, ... of the [lines][cols]
+// rows of a wave's x lines, in row-major order: the row and column, and the
+// element's offset in a field (the caller's dq = 64 / cols and dr = 64 % cols
+// step it without a division).
+struct RowWalk {
+    int r, j, uu;
+    int64_t off;
+    __device__ __forceinline__ RowWalk(int lane, int cols, int line0, int t0, const BiasPass &ps) {
+        r = lane / cols;
+        j = lane - r * cols;
+        const int ln = line0 + r;
+        const int vv = ln / ps.nu;
+        uu = ln - vv * ps.nu;
+        off = (int64_t)uu * ps.su + (int64_t)vv * ps.sv + t0 + j;
     }
-    __device__ __forceinline__ void next(int nu) {
+    __device__ __forceinline__ void next(int cols, int dq, int dr, const BiasPass &ps) {
         int dl = dq;
         j += dr;
+        off += dr;
         if (j >= cols) {
             j -= cols;
+            off -= cols;
             ++dl;
         }
-        l += dl;
-        ln += dl;
+        r += dl;
         uu += dl;
-        while (uu >= nu) {
-            uu -= nu;
-            ++vv;
+        off += (int64_t)dl * ps.su;
+        while (uu >= ps.nu) {
+            uu -= ps.nu;
+            off += (int64_t)ps.sv - (int64_t)ps.nu * ps.su;
         }
     }
 };
 
-// LDS: exchange area [4 waves][2][64], then (x lines) the tile of the
-// workgroup's lines, [4/P groups x 64 lines][pitch].
-// Iterated closures (Eq. iter_left_X and its mirror; ev given): every row of
-// a closure line takes the interior scheme, and the solution entering at node
-// -1 (left bias) / N (right bias) is ev[2 e] / ev[2 e + 1] of the line's
-// entry e = ev_base + field * nlines + line, instead of the closure rows.
-// ends (if given) receives, unscaled (before h^-1), the left-biased solution
-// at node N - 1 and the right-biased one at node 0 of every line, the values
-// the neighbours' next iterate enters with.
-template <typename T, int HB, int L, bool XDIR>
-__global__ __launch_bounds__(256) void k_biased_part(const BiasItem *__restrict__ items,
-                                                     const BiasPass *__restrict__ passes,
-                                                     const T *__restrict__ coefs, const T *__restrict__ in,
-                                                     T *__restrict__ out, const T *__restrict__ ev,
-                                                     T *__restrict__ ends) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// One wave: NW = 64 / P lines of one field of one pass, P = 2^lgP partitions of
+// Lr <= L rows per line (lane = p NW + line), Pu of them holding rows.  Iterated
+// closures (Eq. iter_left_X and its mirror; ev given): every row of a closure
+// line takes the interior scheme, and the solution entering at node -1 (left
+// bias) / N (right bias) is ev[2 e] / ev[2 e + 1] of the line's entry e =
+// ev_base + field * nlines + line, instead of the closure rows.  ends (if
+// given) receives, unscaled (before h^-1), the left-biased solution at node
+// N - 1 and the right-biased one at node 0 of every line, the values the
+// neighbours' next iterate enters with.  Off: byte offsets of a lane's line
+// relative to the item's first line (32 bits where they fit).
+template <typename T, int HB, bool EMB, int L, typename Off>
+__device__ __forceinline__ void bias_wave(const BiasPass &ps, int field, int line0, int lgP, int Lr, int tilew,
+                                          const T *__restrict__ coefs, const T *__restrict__ in, T *__restrict__ out,
+                                          const T *__restrict__ ev, T *__restrict__ ends, T *smem) {
     constexpr int W = L + 2 * HB + 2;   // f[i] = node k0 - HB - 1 + i
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const BiasItem item = items[blockIdx.x];
-    if (item.pass < 0) return;   // padding of the XCD-interleaved order (whole workgroup)
-    const BiasPass ps = passes[item.pass];
-    const int P = item.P, G = 4 / P;
-    const int g = wv / P, p = wv - g * P;
-    const int N = ps.N, Lr = (N + P - 1) / P;
-    const int k0 = p * Lr;
-    const int nrows = min(Lr, N - k0);   // >= 2: the host picks P so that every partition has 2 rows
-    const int line = item.line0 + 64 * g + lane;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int P = 1 << lgP, lgN = 6 - lgP, NW = 64 >> lgP;
+    const int N = ps.N;
+    const int first = line0 + wv * NW;   // this wave's first line
+    if (first >= ps.nlines) return;
+    const int Pu = (N + Lr - 1) / Lr, nlast = N - (Pu - 1) * Lr;   // >= 2 (host)
+    const int p = lane >> lgN, l = lane & (NW - 1);
+    const bool idle = p >= Pu, islast = p == Pu - 1;
+    const int k0 = idle ? 0 : p * Lr;    // idle lanes read partition 0 and take no part
+    int line = first + l;
     const bool active = line < ps.nlines;
-    const int u = active ? line % ps.nu : 0, v = active ? line / ps.nu : 0;
-    const int64_t fbase = ps.in_base + (int64_t)item.field * ps.in_fstride;
-    const int64_t obase = ps.out_base + (int64_t)item.field * ps.out_fstride;
-    T *exch = (T *)smem;
-    T *tile = exch + 4 * 2 * 64;
+    if (!active) line = ps.nlines - 1;
+    const int v0 = first / ps.nu, u0 = first - v0 * ps.nu;
+    const int v = line / ps.nu, u = line - v * ps.nu;
+    const bool xdir = ps.sd == 1;
     const bool periodic = ps.periodic;
     const bool iter = ev != nullptr && !periodic;
-    const bool closureL = !periodic && p == 0 && !iter;
-    const bool closureR = !periodic && p == P - 1 && !iter;
-    const int64_t eix = 2 * (ps.ev_base + (int64_t)item.field * ps.nlines + line);   // this line's end entries
+    const bool closed = !periodic && !iter;
     const int mode = ps.mode;
+    const bool left = mode <= 0 || mode == 2;   // -1 left, 0 upwind, 1 right, 2 symmetrised
+    const bool right = mode >= 0;
     const T *rec = coefs + (int64_t)ps.tab * kBiasRec;
     BCoef<T, HB> q;
     load_coef<T, HB>(q, rec);
     const T alpha = q.alpha;
+    const T *pw = rec + kBiasPow;   // (-alpha)^n
+    T *tile = smem + (int64_t)wv * tilew;
+
+    const int64_t base0 = (int64_t)u0 * ps.su + (int64_t)v0 * ps.sv;   // the wave's first line in a field
+    const int64_t fbase = ps.in_base + (int64_t)field * ps.in_fstride;
+    const int64_t sdB = (int64_t)ps.sd * (int64_t)sizeof(T);
+    const Off voff = (Off)(((int64_t)u * ps.su + (int64_t)v * ps.sv - base0 + (int64_t)k0 * ps.sd) * (int64_t)sizeof(T));
+    const int nval = min(NW, ps.nlines - first);   // real lines of this wave
+    const int dqN = 64 / N, drN = 64 - dqN * N;    // x lines: walk over N columns
+    constexpr int BATCH = 8;
 
     // ---- partition rows and halo into registers
     T f[W];
-    int vp = N | 1;   // x lines: pitch of the velocity / output tile
-    if (XDIR) {
-        int t0, Tn;
-        if (periodic) {
-            t0 = 0;
-            Tn = N;
-        } else {
-            const int e = min(ps.ng, HB + 1);
-            t0 = -e;
-            Tn = N + 2 * e;
+    if (xdir) {
+        const int e = periodic ? 0 : min(ps.ng, HB + 1);
+        const int Tn = N + 2 * e, tp = Tn | 1;
+        const int total = nval * Tn;
+        const int dq = 64 / Tn, dr = 64 - dq * Tn;
+        RowWalk w(lane, Tn, first, -e, ps);
+        const T *src = in + fbase;
+        for (int e0 = lane; e0 < total; e0 += 64 * BATCH) {
+            T val[BATCH];
+            int at[BATCH];
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                at[b] = -1;
+                val[b] = T(0);
+                if (e0 + 64 * b < total) {
+                    at[b] = w.r * tp + w.j;
+                    val[b] = src[w.off];
+                }
+                w.next(Tn, dq, dr, ps);
+            }
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b)
+                if (at[b] >= 0) tile[at[b]] = val[b];
         }
-        const int tp = Tn | 1;
-        const int nl = 64 * G;
-        // consecutive threads take consecutive nodes of the workgroup's rows
-        for (TileWalk w(threadIdx.x, Tn, item.line0, ps.nu); w.l < nl; w.next(ps.nu)) {
-            T val = 0;
-            if (w.ln < ps.nlines) val = in[fbase + (int64_t)w.uu * ps.su + (int64_t)w.vv * ps.sv + (t0 + w.j)];
-            tile[w.l * tp + w.j] = val;
-        }
-        __syncthreads();
-        const T *row = tile + (64 * g + lane) * tp;
+        wave_sync();
+        const T *row = tile + l * tp + k0;
+        const int ilo = HB + 1 - e, ihi = nlast + e + HB + 1;
 #pragma unroll
         for (int i = 0; i < W; ++i) {
-            int j = k0 - HB - 1 + i;
-            if (periodic) {
-                j %= N;
-                if (j < 0) j += N;
-                f[i] = row[j];
-            } else {
-                f[i] = (j >= t0 && j < t0 + Tn) ? row[j - t0] : T(0);
+            f[i] = T(0);
+            if (i < Lr + 2 * HB + 2) {
+                if (periodic) {
+                    int j = k0 - HB - 1 + i;
+                    while (j < 0) j += N;
+                    while (j >= N) j -= N;
+                    f[i] = tile[l * tp + j];
+                } else if (i < ilo || i >= ihi) {
+                    const int j = k0 - HB - 1 + i;
+                    if (j >= -e && j < N + e) f[i] = row[i - ilo];
+                } else {
+                    f[i] = row[i - ilo];
+                }
             }
         }
-        __syncthreads();   // the tile is reused for the velocity and the output
-        if (mode == 0) {
-            for (TileWalk w(threadIdx.x, N, item.line0, ps.nu); w.l < nl; w.next(ps.nu)) {
-                T val = 0;
-                if (w.ln < ps.nlines) val = in[ps.vel_base + (int64_t)w.uu * ps.su + (int64_t)w.vv * ps.sv + w.j];
-                tile[w.l * vp + w.j] = val;
+        wave_sync();   // the tile is reused for the velocity and the output
+    } else if (periodic) {
+        const char *src = (const char *)(in + fbase + base0);
+        const Off lo = (Off)(((int64_t)u * ps.su + (int64_t)v * ps.sv - base0) * (int64_t)sizeof(T));
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            f[i] = T(0);
+            if (i < Lr + 2 * HB + 2) {
+                int j = k0 - HB - 1 + i;
+                while (j < 0) j += N;
+                while (j >= N) j -= N;
+                f[i] = *(const T *)(src + (Off)(lo + (Off)j * (Off)sdB));
             }
         }
     } else {
-        BLine<T> Lf{in + fbase + (int64_t)u * ps.su + (int64_t)v * ps.sv, ps.sd, N, ps.ng, periodic};
+        // nodes outside the stored line (a class wider than the scheme, or the
+        // missing rows of the last partition) read as 0
+        const char *src = (const char *)(in + fbase + base0) - (HB + 1) * sdB;
+        const int ilo = HB + 1 - ps.ng, ihi = nlast + ps.ng + HB + 1;
 #pragma unroll
-        for (int i = 0; i < W; ++i) f[i] = active ? Lf.ld(k0 - HB - 1 + i) : T(0);
+        for (int i = 0; i < W; ++i) {
+            f[i] = T(0);
+            if (i < Lr + 2 * HB + 2) {
+                if (i < ilo || i >= ihi) {
+                    const int j = k0 - HB - 1 + i;
+                    if (j >= -ps.ng && j < N + ps.ng) f[i] = *(const T *)(src + voff);
+                } else {
+                    f[i] = *(const T *)(src + voff);
+                }
+            }
+            src += sdB;
+        }
     }
 
-    // ---- right-hand sides (closure rows where this partition holds them)
-    T rl[L], rr[L];
+    // velocity of x lines: through the tile, read back in partition order below
+    const int vp = N | 1;
+    T *trow = tile + l * vp + k0;
+    if (xdir && mode == 0) {
+        const int total = nval * N;
+        RowWalk w(lane, N, first, 0, ps);
+        const T *src = in + ps.vel_base;
+        for (int e0 = lane; e0 < total; e0 += 64 * BATCH) {
+            T val[BATCH];
+            int at[BATCH];
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-        rl[i] = (closureL && i == 0) ? left_closure<T, HB>(q, f + i) : left_interior<T, HB>(q, f + i);
-        rr[i] = (closureR && i == nrows - 1) ? right_closure<T, HB>(q, f + i) : right_interior<T, HB>(q, f + i);
+            for (int b = 0; b < BATCH; ++b) {
+                at[b] = -1;
+                val[b] = T(0);
+                if (e0 + 64 * b < total) {
+                    at[b] = w.r * vp + w.j;
+                    val[b] = src[w.off];
+                }
+                w.next(N, dqN, drN, ps);
+            }
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b)
+                if (at[b] >= 0) tile[at[b]] = val[b];
+        }
+        wave_sync();
     }
-    if ((ps.s2 || ps.s2_in) && active) {   // W, U: the second-derivative term of each row
-        const T *s2 = (ps.s2_in ? in : (const T *)ps.s2) + ps.s2_base + (int64_t)item.field * ps.s2f +
-                      (int64_t)u * ps.s2u + (int64_t)v * ps.s2v;
-        const T w2 = (T)ps.w2, w2c = (T)ps.w2c;
+
+    // scans over a line's partitions of v = (value leaving the partition for a
+    // zero entering value): lane p's v becomes the value leaving it for a zero
+    // value entering the line; wL = the entering value's weight per partition
+    auto scan_up = [&](T vv, T wL) {
+        for (int s = 1; s < P; s <<= 1) {
+            const T t = __shfl(vv, lane - s * NW);
+            if (p >= s) vv += wL * t;
+            wL *= wL;
+        }
+        return vv;
+    };
+    auto scan_down = [&](T vv, T wL) {
+        for (int s = 1; s < P; s <<= 1) {
+            const T t = __shfl(vv, lane + s * NW);
+            if (p + s < P) vv += wL * t;
+            wL *= wL;
+        }
+        return vv;
+    };
+    const int lastlane = (Pu - 1) * NW + l;
+
+    // ---- right-hand sides (closure rows where this lane holds them)
+    const bool closureL = closed && p == 0;
+    const bool closureR = closed && islast;
+    T rl[L], rr[L];
+    if constexpr (EMB) {
+        // W: the compact second derivative (2)P1_M on the same rows, explicit
+        // closure rows.  [a2, 1, a2] = (1 + b S-)(1 + b S+) b / a2 on the infinite
+        // line, so it is a forward and a backward recurrence over the line
+        // with zero right side on the closure rows, and the closure values
+        // are met with the two homogeneous solutions (-b)^k, (-b)^(N-1-k).
+        const T beta = rec[25], kappa = rec[26];
+        const T *pb = rec + kBiasPow2;   // (-beta)^n
+        const T *st = rec + kBiasSt2, *sc = rec + kBiasCl2;
+        T s[L];
+        T e0 = T(0), e1 = T(0);
+        {
+            T up = T(0), uF = T(0), uN = T(0);
+#pragma unroll
+            for (int i = 0; i < L; ++i) {
+                s[i] = T(0);
+                if (i < Lr) {
+                    T r = st[5] * f[HB + 1 + i];
+#pragma unroll
+                    for (int m = 1; m <= (HB < 3 ? HB + 1 : 3); ++m)
+                        r += st[5 + m] * (f[HB + 1 + i + m] + f[HB + 1 + i - m]);
+                    r *= kappa;
+                    constexpr int MC = HB + 1 < 5 ? HB + 1 : 5;
+                    if (i == 0 && closed) {
+                        T c = T(0);
+#pragma unroll
+                        for (int m = -MC; m <= MC; ++m) c += sc[5 + m] * f[HB + 1 + i + m];
+                        e0 = c;
+                        if (p == 0) r = T(0);
+                    }
+                    if (i >= nlast - 1) {
+                        if (i == nlast - 1 && closed) {
+                            T c = T(0);
+#pragma unroll
+                            for (int m = -MC; m <= MC; ++m) c += sc[5 - m] * f[HB + 1 + i + m];
+                            e1 = c;
+                            if (islast) r = T(0);
+                        }
+                        if (i > nlast - 1 && islast) r = T(0);
+                    }
+                    const T uu = r - beta * up;
+                    s[i] = uu;
+                    up = uu;
+                    if (i == Lr - 1) uF = uu;
+                    if (i == nlast - 1) uN = uu;
+                }
+            }
+            const T vU = scan_up(uF, pb[Lr]);
+            T U = __shfl(vU, lane - NW);
+            if (p == 0) U = T(0);
+            if (periodic) {
+                const T xN = __shfl(uN + pb[nlast] * U, lastlane) * (T)ps.wrap2;
+                U += pb[k0] * xN;
+            }
+#pragma unroll
+            for (int i = 0; i < L; ++i)
+                if (i < Lr) s[i] += pb[i + 1] * U;
+        }
+        T sn = T(0), sN = T(0);
+#pragma unroll
+        for (int i = L - 1; i >= 0; --i)
+            if (i < Lr) {
+                T x = s[i] - beta * sn;
+                if (i >= nlast && islast) x = T(0);
+                if (i == nlast - 1) sN = x;
+                s[i] = x;
+                sn = x;
+            }
+        const T vS = scan_down(idle ? T(0) : s[0], pb[Lr]);
+        T S = __shfl(vS, lane + NW);
+        if (p + 1 >= P) S = T(0);
+        T K1 = T(0), K2 = T(0);
+        if (periodic) {
+            const T x0 = __shfl(vS, l) * (T)ps.wrap2;
+            S += pb[islast || idle ? 0 : N - k0 - Lr] * x0;
+        } else {
+            const T d0 = __shfl(e0, l) - __shfl(vS, l);
+            const T d1 = __shfl(e1, lastlane) - __shfl(sN, lastlane);
+            const T bN = pb[N - 1];
+            K1 = (d0 - bN * d1) * (T)ps.det2 * pb[k0];
+            K2 = (d1 - bN * d0) * (T)ps.det2;
+            if (!islast && !idle) K2 *= pb[N - k0 - Lr];
+        }
+        // the last partition's rows count from its own end, nlast rows in
+        K2 -= beta * S;
+        if (islast) K2 *= (T)1 / pb[Lr - nlast];
 #pragma unroll
         for (int i = 0; i < L; ++i) {
-            if (i < nrows) {
-                const T e = s2[(int64_t)(k0 + i) * ps.s2d];
-                rl[i] += ((closureL && i == 0) ? w2c : w2) * e;
-                rr[i] -= ((closureR && i == nrows - 1) ? w2c : w2) * e;
+            rl[i] = rr[i] = T(0);
+            if (i < Lr) {
+                const T e = (T)ps.w2 * (s[i] + K1 * pb[i] + K2 * pb[Lr - 1 - i]);
+                rl[i] = left_interior<T, HB>(q, f + i) + e;
+                rr[i] = right_interior<T, HB>(q, f + i) - e;
+                if (i == 0 && closed) {
+                    const T c = left_closure<T, HB>(q, f + i);
+                    if (closureL) rl[i] = c;
+                }
+                if (i == nlast - 1 && closed) {
+                    const T c = right_closure<T, HB>(q, f + i);
+                    if (closureR) rr[i] = c;
+                }
             }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            rl[i] = rr[i] = T(0);
+            if (i < Lr) {
+                rl[i] = left_interior<T, HB>(q, f + i);
+                rr[i] = right_interior<T, HB>(q, f + i);
+                if (i == 0 && closed) {
+                    const T c = left_closure<T, HB>(q, f + i);
+                    if (closureL) rl[i] = c;
+                }
+                if (i == nlast - 1 && closed) {
+                    const T c = right_closure<T, HB>(q, f + i);
+                    if (closureR) rr[i] = c;
+                }
+            }
+        }
+        if (ps.s2_in && !idle) {   // U: the sampled second derivative, on every row
+            const T *s2 = in + ps.s2_base + (int64_t)u * ps.s2u + (int64_t)v * ps.s2v + (int64_t)k0 * ps.s2d;
+            const T w2 = (T)ps.w2, w2c = (T)ps.w2c;
+#pragma unroll
+            for (int i = 0; i < L; ++i)
+                if (i < Lr && !(i >= nlast && islast)) {
+                    const T e = s2[(int64_t)i * ps.s2d];
+                    rl[i] += ((closureL && i == 0) ? w2c : w2) * e;
+                    rr[i] -= ((closureR && i == nlast - 1) ? w2c : w2) * e;
+                }
         }
     }
 
     // ---- local solves with zero entering values
-    T xl_last = 0, xr_first = 0;
-    const bool left = mode <= 0 || mode == 2;   // -1 left, 0 upwind, 2 symmetrised: the left-biased solve
+    T xlF = T(0), xlN = T(0);
     if (left) {
-        T xp = 0;
+        T xp = T(0);
 #pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const T x = (closureL && i == 0) ? (rl[0] - alpha * rl[1]) * q.inv_det : rl[i] - alpha * xp;
-            rl[i] = x;
-            xp = x;
-            if (i == nrows - 1) xl_last = x;
-        }
+        for (int i = 0; i < L; ++i)
+            if (i < Lr) {
+                T x = rl[i] - alpha * xp;
+                if (i == 0 && closureL) x = (rl[0] - alpha * rl[1]) * q.inv_det;
+                rl[i] = x;
+                xp = x;
+                if (i == Lr - 1) xlF = x;
+                if (i == nlast - 1) xlN = x;
+            }
     }
-    if (mode >= 0) {
-        T xn = 0;
+    if (right) {
+        T xn = T(0);
 #pragma unroll
-        for (int i = L - 1; i >= 0; --i) {
-            T x;
-            if (i >= nrows) x = 0;
-            else if (closureR && i == nrows - 1) x = (rr[i] - alpha * (i > 0 ? rr[i > 0 ? i - 1 : 0] : T(0))) * q.inv_det;
-            else x = rr[i] - alpha * xn;
-            rr[i] = x;
-            xn = x;
-        }
-        xr_first = rr[0];
+        for (int i = L - 1; i >= 0; --i)
+            if (i < Lr) {
+                T x = rr[i] - alpha * xn;
+                if (i > 0 && i == nlast - 1 && closureR) x = (rr[i] - alpha * rr[i > 0 ? i - 1 : 0]) * q.inv_det;
+                if (i >= nlast && islast) x = T(0);
+                rr[i] = x;
+                xn = x;
+            }
     }
-    // velocity of y/z lines: loaded here so that the loads overlap the exchange
+    // velocity of y/z lines: requested here so that the loads overlap the scans
     T c[L];
-    if (!XDIR && mode == 0) {
-        const T *vl = in + ps.vel_base + (int64_t)u * ps.su + (int64_t)v * ps.sv;
+    if (mode == 0) {
+        if (xdir) {
 #pragma unroll
-        for (int i = 0; i < L; ++i) c[i] = (active && i < nrows) ? vl[(int64_t)(k0 + i) * ps.sd] : T(0);
+            for (int i = 0; i < L; ++i) c[i] = (i < Lr) ? trow[i] : T(0);
+        } else {
+            const char *vl = (const char *)(in + ps.vel_base + base0);
+#pragma unroll
+            for (int i = 0; i < L; ++i) {
+                c[i] = T(0);
+                if (i < Lr) {
+                    if (i < nlast) c[i] = *(const T *)(vl + voff);
+                    else if (!islast) c[i] = *(const T *)(vl + voff);
+                }
+                vl += sdB;
+            }
+        }
     }
-    exch[(wv * 2 + 0) * 64 + lane] = xl_last;
-    exch[(wv * 2 + 1) * 64 + lane] = xr_first;
-    __syncthreads();
 
     // ---- true values entering the partition
-    const T *pw = rec + kBiasPow;   // (-alpha)^n
-    T X = 0, Y = 0;
-    if (iter && active) {   // the values entering the line, from the neighbours' previous iterate
-        X = ev[eix];
-        Y = ev[eix + 1];
-    }
+    T X = T(0), Y = T(0);
+    const int64_t eix = 2 * (ps.ev_base + (int64_t)field * ps.nlines + line);   // this line's end entries
     if (left) {
-        if (periodic) {
-            T s = 0;
-            for (int qq = 0; qq < P; ++qq) {
-                const int k1 = min(qq * Lr + Lr, N) - 1;
-                s += pw[N - 1 - k1] * exch[((g * P + qq) * 2 + 0) * 64 + lane];
-            }
-            X = s * (T)ps.wrap;
-        }
-        for (int qq = 0; qq < p; ++qq) X = exch[((g * P + qq) * 2 + 0) * 64 + lane] + pw[min(Lr, N - qq * Lr)] * X;
+        X = __shfl(scan_up(xlF, pw[Lr]), lane - NW);
+        if (p == 0) X = T(0);
+        if (periodic) X += pw[k0] * (__shfl(xlN + pw[nlast] * X, lastlane) * (T)ps.wrap);
+        if (iter) X += pw[k0] * ev[eix];
+        if (ends && !periodic && active && islast) ends[eix] = xlN + pw[nlast] * X;
     }
-    if (mode >= 0) {
-        if (periodic) {
-            T s = 0;
-            for (int qq = 0; qq < P; ++qq) s += pw[qq * Lr] * exch[((g * P + qq) * 2 + 1) * 64 + lane];
-            Y = s * (T)ps.wrap;
-        }
-        for (int qq = P - 1; qq > p; --qq) Y = exch[((g * P + qq) * 2 + 1) * 64 + lane] + pw[min(Lr, N - qq * Lr)] * Y;
-    }
-
-    // ---- the line's end values for the neighbours' next iterate (unscaled)
-    if (ends && active && !periodic) {
-        if (left && p == P - 1) ends[eix] = rl[nrows - 1] + pw[nrows] * X;
-        if (mode >= 0 && p == 0) ends[eix + 1] = rr[0] + pw[nrows] * Y;
+    if (right) {
+        const T vR = scan_down(idle ? T(0) : rr[0], pw[Lr]);
+        Y = __shfl(vR, lane + NW);
+        if (p + 1 >= P) Y = T(0);
+        const int up = (islast || idle) ? 0 : N - k0 - Lr;   // rows above this partition
+        if (periodic) Y += pw[up] * (__shfl(vR, l) * (T)ps.wrap);
+        if (iter) Y += pw[up] * ev[eix + 1];
+        const int nr0 = Pu == 1 ? nlast : Lr;
+        if (ends && !periodic && active && p == 0) ends[eix + 1] = rr[0] + pw[nr0] * Y;
+        // the last partition's rows count from its own end, nlast rows in
+        if ((periodic || iter) && islast && nlast < Lr && alpha != T(0)) Y *= (T)1 / pw[Lr - nlast];
     }
 
     // ---- corrected values, combined and stored
     const T hinv = (T)ps.hinv;
-    T *tl = tile + (64 * g + lane) * vp;
+    const int64_t obase0 = (int64_t)u0 * ps.osu + (int64_t)v0 * ps.osv;
+    const int64_t osdB = (int64_t)ps.osd * (int64_t)sizeof(T);
+    char *dst = (char *)(out + ps.out_base + (int64_t)field * ps.out_fstride + obase0);
+    const Off ovoff =
+        (Off)(((int64_t)u * ps.osu + (int64_t)v * ps.osv - obase0 + (int64_t)k0 * ps.osd) * (int64_t)sizeof(T));
+    const bool keep = !idle && (xdir || active);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-        if (i < nrows) {
+        if (i < Lr) {
             T val;
             if (mode < 0) {
                 val = hinv * (rl[i] + pw[i + 1] * X);
             } else if (mode == 1) {
-                val = hinv * (rr[i] + pw[nrows - i] * Y);
+                val = hinv * (rr[i] + pw[Lr - i] * Y);
             } else if (mode == 2) {
-                val = T(0.5) * (hinv * (rl[i] + pw[i + 1] * X) + hinv * (rr[i] + pw[nrows - i] * Y));
+                val = T(0.5) * (hinv * (rl[i] + pw[i + 1] * X) + hinv * (rr[i] + pw[Lr - i] * Y));
             } else {
-                const T cv = XDIR ? tl[k0 + i] : c[i];
                 const T xL = rl[i] + pw[i + 1] * X;
-                const T xR = rr[i] + pw[nrows - i] * Y;
-                val = fmin(cv, (T)0) * (hinv * xR) + fmax(cv, (T)0) * (hinv * xL);
+                const T xR = rr[i] + pw[Lr - i] * Y;
+                val = fmin(c[i], (T)0) * (hinv * xR) + fmax(c[i], (T)0) * (hinv * xL);
             }
-            if (XDIR) tl[k0 + i] = val;
-            else if (active) out[obase + (int64_t)u * ps.osu + (int64_t)v * ps.osv + (int64_t)(k0 + i) * ps.osd] = val;
+            if (keep && !(i >= nlast && islast)) {
+                if (xdir) trow[i] = val;
+                else __builtin_nontemporal_store(val, (T *)(dst + ovoff));
+            }
+        }
+        dst += osdB;
+    }
+    if (xdir) {   // the rows of consecutive x lines are contiguous in the output
+        wave_sync();
+        const int total = nval * N;
+        T *orow = out + ps.out_base + (int64_t)field * ps.out_fstride + (int64_t)first * N;
+        int r = lane / N, j = lane - r * N;
+#pragma unroll 4
+        for (int e = lane; e < total; e += 64) {
+            __builtin_nontemporal_store(tile[r * vp + j], orow + e);
+            j += drN;
+            r += dqN;
+            if (j >= N) {
+                j -= N;
+                ++r;
+            }
         }
     }
-    if (XDIR) {
-        __syncthreads();
-        const int nl = 64 * G;
-        for (TileWalk w(threadIdx.x, N, item.line0, ps.nu); w.l < nl; w.next(ps.nu))
-            if (w.ln < ps.nlines) out[obase + (int64_t)w.uu * ps.osu + (int64_t)w.vv * ps.osv + w.j] = tile[w.l * vp + w.j];
+}
+
+template <typename T, int HB, bool EMB, typename Off, int L0, int... Ls>
+__device__ __forceinline__ void bias_dispatch(int code, const BiasPass &ps, int field, int line0, int lgP, int Lr,
+                                              int tilew, const T *coefs, const T *in, T *out, const T *ev, T *ends,
+                                              T *smem) {
+    if (code == 0) {
+        bias_wave<T, HB, EMB, L0, Off>(ps, field, line0, lgP, Lr, tilew, coefs, in, out, ev, ends, smem);
+        return;
     }
+    if constexpr (sizeof...(Ls) > 0)
+        bias_dispatch<T, HB, EMB, Off, Ls...>(code - 1, ps, field, line0, lgP, Lr, tilew, coefs, in, out, ev, ends,
+                                              smem);
+}
+
+// Work item meta: lgP in bits 0..3, Lr in bits 4..11, index of L in the
+// kernel's compiled set in bits 12..15.  tilew: elements of one wave's tile.
+template <typename T, int HB, bool EMB, typename Off, int... Ls>
+__global__ __launch_bounds__(256) void k_biased_wave(const BiasItem *__restrict__ items,
+                                                     const BiasPass *__restrict__ passes,
+                                                     const T *__restrict__ coefs, const T *__restrict__ in,
+                                                     T *__restrict__ out, const T *__restrict__ ev,
+                                                     T *__restrict__ ends, int tilew) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const BiasItem item = items[blockIdx.x];
+    if (item.pass < 0) return;   // padding of the XCD-interleaved order (whole workgroup)
+    bias_dispatch<T, HB, EMB, Off, Ls...>((item.meta >> 12) & 15, passes[item.pass], item.field, item.line0,
+                                          item.meta & 15, (item.meta >> 4) & 255, tilew, coefs, in, out, ev, ends,
+                                          (T *)smem);
 }
 
 template <typename T, int HB>
@@ -392,11 +658,8 @@ __global__ __launch_bounds__(256) void k_biased(const BiasItem *__restrict__ ite
     const T hinv = (T)ps.hinv;
     const T alpha = q.alpha;
     T w[W];
-    // W, U: the second-derivative term at node k, interior rows (e2) and closure row (e2c)
-    const T *s2 = (ps.s2 || ps.s2_in) ? (ps.s2_in ? in : (const T *)ps.s2) + ps.s2_base +
-                                            (int64_t)item.field * ps.s2f + (int64_t)u * ps.s2u +
-                                            (int64_t)v * ps.s2v
-                                      : nullptr;
+    // U: the second-derivative term at node k, interior rows (e2) and closure row (e2c)
+    const T *s2 = ps.s2_in ? in + ps.s2_base + (int64_t)u * ps.s2u + (int64_t)v * ps.s2v : nullptr;
     const T w2 = (T)ps.w2, w2c = (T)ps.w2c;
     auto e2 = [&](int k) -> T { return s2 ? w2 * s2[(int64_t)k * ps.s2d] : T(0); };
     auto e2c = [&](int k) -> T { return s2 ? w2c * s2[(int64_t)k * ps.s2d] : T(0); };
@@ -506,21 +769,26 @@ const void *sweep_fn(int hb) {
     }
 }
 
+// The wave kernel's instances: partitions of up to 8 or 12 rows (set 0), of up
+// to 16 (set 1); with or without an embedded second derivative; 64-bit offsets
+// for fields of 4 GiB and more.
 template <typename T, int HB>
-const void *part_fn_hb(int L, int xdir) {
-    if (L == 8) return xdir ? (const void *)k_biased_part<T, HB, 8, true> : (const void *)k_biased_part<T, HB, 8, false>;
-    if (L == 12) return xdir ? (const void *)k_biased_part<T, HB, 12, true> : (const void *)k_biased_part<T, HB, 12, false>;
-    if (L == 16) return xdir ? (const void *)k_biased_part<T, HB, 16, true> : (const void *)k_biased_part<T, HB, 16, false>;
-    return nullptr;
+const void *wave_fn_hb(int set, int emb, int big) {
+    if (big) {
+        if (set) return emb ? (const void *)k_biased_wave<T, HB, true, uint64_t, 16> : (const void *)k_biased_wave<T, HB, false, uint64_t, 16>;
+        return emb ? (const void *)k_biased_wave<T, HB, true, uint64_t, 8, 12> : (const void *)k_biased_wave<T, HB, false, uint64_t, 8, 12>;
+    }
+    if (set) return emb ? (const void *)k_biased_wave<T, HB, true, uint32_t, 16> : (const void *)k_biased_wave<T, HB, false, uint32_t, 16>;
+    return emb ? (const void *)k_biased_wave<T, HB, true, uint32_t, 8, 12> : (const void *)k_biased_wave<T, HB, false, uint32_t, 8, 12>;
 }
 
 template <typename T>
-const void *part_fn(int hb, int L, int xdir) {
+const void *wave_fn(int hb, int set, int emb, int big) {
     switch (hb) {
-        case 2: return part_fn_hb<T, 2>(L, xdir);
-        case 3: return part_fn_hb<T, 3>(L, xdir);
-        case 4: return part_fn_hb<T, 4>(L, xdir);
-        case 5: return part_fn_hb<T, 5>(L, xdir);
+        case 2: return wave_fn_hb<T, 2>(set, emb, big);
+        case 3: return wave_fn_hb<T, 3>(set, emb, big);
+        case 4: return wave_fn_hb<T, 4>(set, emb, big);
+        case 5: return wave_fn_hb<T, 5>(set, emb, big);
         default: return nullptr;
     }
 }
@@ -529,16 +797,34 @@ const void *part_fn(int hb, int L, int xdir) {
 
 bool biased_supported(int hb) { return hb >= 2 && hb <= 5; }
 
-size_t biased_lds(int f32, int hb, int L, int xdir, int P, int N) {
-    if (L == 0) return 0;
-    const size_t es = f32 ? 4 : 8;
-    size_t b = 4 * 2 * 64 * es;
-    if (xdir) {
-        const int e = hb + 1;   // at most this many ghost nodes per side are staged
-        const int tp = (N + 2 * e) | 1;
-        b += (size_t)(4 / P) * 64 * (size_t)std::max(tp, N | 1) * es;
+// The fewest partitions of at most 12 rows (16 on lines of more than 192
+// nodes), rows spread evenly, the last partition keeping at least two (its
+// closure rows are solved together): fewer partitions keep the stencil halo's
+// share of the loads down, and 12 rows of a pair of biases are what fits half
+// of a wave's registers.  y and z lines stop at 16 partitions: with fewer than
+// 4 lines per wave their accesses cover less than 32 contiguous bytes, and the
+// sweep kernel, 64 lines per wave, is the better one.
+bool bias_split(int N, int dir, BiasSplit &s) {
+    if (N < 2) return false;
+    for (int lg = 0; lg <= (dir == 0 ? 6 : 4); ++lg) {
+        const int cap = (lg == 4 && N > 192) || lg > 4 ? 16 : 12;
+        for (int Lr = std::max(2, (N + (1 << lg) - 1) >> lg); Lr <= cap; ++Lr) {
+            const int Pu = (N + Lr - 1) / Lr;
+            if (N - (Pu - 1) * Lr < 2) continue;
+            s.lgP = lg;
+            s.Lr = Lr;
+            s.set = Lr > 12;
+            s.code = s.set ? 0 : Lr > 8;
+            return true;
+        }
     }
-    return b;
+    return false;
+}
+
+int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, int N) {
+    if (dir != 0) return 0;
+    const int e = periodic ? 0 : std::min(ng, hb + 1);
+    return (64 >> s.lgP) * ((N + 2 * e) | 1);
 }
 
 // End values of the next iterate: for every biased pass (rec = ev base of
@@ -565,38 +851,38 @@ hipError_t launch_bias_gather(int f32, int npass, int64_t max_entries, const int
     return hipGetLastError();
 }
 
-hipError_t launch_biased(int f32, int hb, int L, int xdir, size_t lds, const BiasItem *items, int nitems,
-                         const BiasPass *passes, const void *coefs, const void *in, void *out, const void *ev,
-                         void *ends, hipStream_t st) {
-    if (nitems <= 0) return hipSuccess;
-    if (L == 0) {
-        const int grid = (nitems + 3) / 4;
-        const void *fn = f32 ? sweep_fn<float>(hb) : sweep_fn<double>(hb);
+hipError_t launch_biased(int f32, const BiasLaunch &g, const BiasItem *items, const BiasPass *passes,
+                         const void *coefs, const void *in, void *out, const void *ev, void *ends, hipStream_t st) {
+    if (g.nitems <= 0) return hipSuccess;
+    if (g.sweep) {
+        const int grid = (g.nitems + 3) / 4;
+        const void *fn = f32 ? sweep_fn<float>(g.hb) : sweep_fn<double>(g.hb);
         if (!fn) return hipErrorInvalidValue;
         if (f32)
             hipLaunchKernelGGL(((void (*)(const BiasItem *, int, const BiasPass *, const float *, const float *,
                                           float *))fn),
-                               dim3(grid), dim3(256), 0, st, items, nitems, passes, (const float *)coefs,
+                               dim3(grid), dim3(256), 0, st, items, g.nitems, passes, (const float *)coefs,
                                (const float *)in, (float *)out);
         else
             hipLaunchKernelGGL(((void (*)(const BiasItem *, int, const BiasPass *, const double *, const double *,
                                           double *))fn),
-                               dim3(grid), dim3(256), 0, st, items, nitems, passes, (const double *)coefs,
+                               dim3(grid), dim3(256), 0, st, items, g.nitems, passes, (const double *)coefs,
                                (const double *)in, (double *)out);
         return hipGetLastError();
     }
-    const void *fn = f32 ? part_fn<float>(hb, L, xdir) : part_fn<double>(hb, L, xdir);
+    const void *fn = f32 ? wave_fn<float>(g.hb, g.set, g.emb, g.big) : wave_fn<double>(g.hb, g.set, g.emb, g.big);
     if (!fn) return hipErrorInvalidValue;
+    const size_t lds = (size_t)4 * g.tilew * (f32 ? 4 : 8);
     if (f32)
         hipLaunchKernelGGL(((void (*)(const BiasItem *, const BiasPass *, const float *, const float *, float *,
-                                      const float *, float *))fn),
-                           dim3(nitems), dim3(256), lds, st, items, passes, (const float *)coefs, (const float *)in,
-                           (float *)out, (const float *)ev, (float *)ends);
+                                      const float *, float *, int))fn),
+                           dim3(g.nitems), dim3(256), lds, st, items, passes, (const float *)coefs, (const float *)in,
+                           (float *)out, (const float *)ev, (float *)ends, g.tilew);
     else
         hipLaunchKernelGGL(((void (*)(const BiasItem *, const BiasPass *, const double *, const double *, double *,
-                                      const double *, double *))fn),
-                           dim3(nitems), dim3(256), lds, st, items, passes, (const double *)coefs,
-                           (const double *)in, (double *)out, (const double *)ev, (double *)ends);
+                                      const double *, double *, int))fn),
+                           dim3(g.nitems), dim3(256), lds, st, items, passes, (const double *)coefs,
+                           (const double *)in, (double *)out, (const double *)ev, (double *)ends, g.tilew);
     return hipGetLastError();
 }
 

@@ -142,12 +142,7 @@ struct cfd_plan {
     DevBuf d_dense, d_dense_specs;        // dense mixed-precision tables
     // biased (upwind) operators: one pass per (block, op), work items grouped
     // by stencil half-width class, coefficient records per op
-    struct BGroup {
-        int hb = 0, L = 0, xdir = 0;   // L = 0: sweep kernel
-        size_t lds = 0;
-        int64_t item0 = 0, nitems = 0;
-    };
-    std::vector<BGroup> bgroups;
+    std::vector<BiasLaunch> bgroups;
     int64_t nbitems = 0;
     DevBuf d_bpass, d_bitems, d_bcoef;
     // iterated biased closures: per biased pass its block, operator and end
@@ -156,16 +151,17 @@ struct cfd_plan {
     std::vector<std::array<int64_t, 4>> bpinfo;   // block, op, ev_base, entries
     int64_t bev_entries = 0, bev_max = 0;
     DevBuf d_bev, d_bends, d_bgrecs;
-    // scratch of the mixed derivatives' first stage and of the W operators'
-    // embedded second derivative (elements)
+    // scratch of the mixed derivatives' first stage (elements)
     int64_t mscr_elems = 0;
     DevBuf d_mscr;
     int64_t n_mixed = 0;                  // (block, mixed-derivative operator) pairs
-    // W operators: scheme index of the embedded (2)P1_M per op (-1: none), and
-    // per (block, op) the scratch offset of its first field's h^-2 (2)P1_M f,
-    // written by line passes that run before the biased launches
+    // W operators: scheme index of the embedded (2)P1_M per op (-1: none; the
+    // biased kernel solves it itself), and the lines it runs along as passes
+    // of the centred kernel: line lengths that have no such kernel are refused,
+    // and schedules may name their partitions
     std::vector<int> emb_sch;
-    std::map<std::pair<int, int>, int64_t> emb_off;
+    std::vector<PassHost> emb_lines;
+    bool has_emb() const { return std::any_of(emb_sch.begin(), emb_sch.end(), [](int e) { return e >= 0; }); }
     std::vector<Group> groups;
     int64_t nitems = 0;
     hipStream_t cap_stream = nullptr;
@@ -1045,6 +1041,7 @@ cfd_status build_biased(cfd_plan *p) {
     p->nbitems = 0;
     if (bops.empty()) return CFD_OK;
     std::vector<double> rec64(bops.size() * kBiasRec, 0.0);
+    std::vector<double> betas(bops.size(), 0.0);
     for (size_t i = 0; i < bops.size(); ++i) {
         const Scheme &s = p->schemes[bops[i]];
         double *r = rec64.data() + i * kBiasRec;
@@ -1053,15 +1050,44 @@ cfd_status build_biased(cfd_plan *p) {
         for (int m = 0; m < 2 * kBiasHalf + 2; ++m) r[12 + m] = s.bc[m];
         r[24] = 1.0 / (1.0 - s.balpha * s.balpha);
         double pw = 1.0;
-        for (int n = 0; n <= kBiasMaxPN; ++n, pw *= -s.balpha) r[kBiasPow + n] = pw;
+        for (int n = 0; n <= kBiasMaxPow; ++n, pw *= -s.balpha) r[kBiasPow + n] = pw;
+        if (p->emb_sch[bops[i]] >= 0) {
+            const Scheme &e2 = p->schemes[p->emb_sch[bops[i]]];
+            const double a2 = e2.lhs[kMaxNL + 1];
+            const int hb = s.bhalf < 2 ? 2 : s.bhalf;
+            // the kernel's bounds: interior half-width 3, closure half-width hb + 1, one implicit neighbour
+            if (e2.nl != 1 || !(a2 > 0 && a2 < 0.5) || e2.m > 3 || e2.mc > std::min(hb + 1, kMaxHalf))
+                return fail(CFD_EUNSUPPORTED, "biased operator: embedded second derivative outside the kernel's bounds");
+            betas[i] = (1.0 - std::sqrt(1.0 - 4.0 * a2 * a2)) / (2.0 * a2);
+            r[25] = betas[i];
+            r[26] = betas[i] / a2;
+            for (int m = 0; m < 2 * kMaxHalf + 1; ++m) {
+                r[kBiasSt2 + m] = e2.rhs[m];
+                r[kBiasCl2 + m] = e2.cl[0][m];
+            }
+            pw = 1.0;
+            for (int n = 0; n <= kBiasMaxPow; ++n, pw *= -betas[i]) r[kBiasPow2 + n] = pw;
+        }
     }
+    for (const PassHost &ps : p->emb_lines)
+        if (candidate_Ps(ps, f32, p->max_lds).empty()) {
+            char buf[200];
+            std::snprintf(buf, sizeof buf,
+                          "no compiled line kernel for N=%d nl=%d nops=%d (stencil half-width %d, direction %d)",
+                          ps.N, ps.nl, ps.nops, ps.hw, ps.dir);
+            return fail(CFD_EUNSUPPORTED, buf);
+        }
     std::vector<BiasPass> bp;
     int64_t ev_total = 0;
     p->bpinfo.clear();
-    // kernel class (hb, L, x lines) -> items; L = 0 is the sweep kernel
-    std::map<std::array<int, 3>, std::vector<BiasItem>> by_cls;
-    std::map<std::array<int, 3>, size_t> cls_lds;
-    std::map<std::array<int, 3>, std::vector<int>> by_unit;   // first item of each unit
+    // passes per block in operator order, with their split
+    struct PassPlan {
+        BiasLaunch g;        // launch class (no items)
+        BiasSplit sp;
+        int op, step, meta;
+        int64_t cost;        // nodes of one field
+    };
+    std::vector<PassPlan> pp;
     for (size_t b = 0; b < p->blocks.size(); ++b) {
         const cfd_block &bl = p->blocks[b];
         const int64_t npts = (int64_t)bl.n[0] * bl.n[1] * bl.n[2];
@@ -1104,20 +1130,14 @@ cfd_status build_biased(cfd_plan *p) {
             q.hinv = 1.0 / bl.h[op.dir];
             q.wrap = 1.0 / (1.0 - std::pow(-s.balpha, (double)d.N));
             q.ev_base = ev_total;
-            q.s2 = nullptr;
-            q.s2_base = q.s2f = 0;
+            q.s2_base = 0;
             q.s2u = q.s2v = q.s2d = q.s2_in = 0;
-            q.w2 = q.w2c = 0.0;
+            q.w2 = q.w2c = q.wrap2 = q.det2 = 0.0;
             const double h2 = bl.h[op.dir] * bl.h[op.dir];
-            if (p->emb_sch[o] >= 0) {   // W: the embedded pass's result in scratch
-                const int f0e = op.field < 0 ? 0 : op.field;
-                q.s2 = p->d_mscr.p;
-                q.s2_base = p->emb_off.at(std::make_pair((int)b, o)) - (int64_t)f0e * npts;
-                q.s2f = d.out_fstride;
-                q.s2u = d.osu;
-                q.s2v = d.osv;
-                q.s2d = d.osd;
-                q.w2 = s.ba2 * h2;
+            if (p->emb_sch[o] >= 0) {   // W: solved in the kernel at unit spacing
+                q.w2 = s.ba2;
+                q.wrap2 = 1.0 / (1.0 - std::pow(-betas[i], (double)d.N));
+                q.det2 = 1.0 / (1.0 - std::pow(betas[i], 2.0 * (d.N - 1)));
             } else if (s.hermite) {     // U: the sampled f'' field of the input
                 q.s2_in = 1;
                 q.s2_base = d.in_base + (int64_t)op.aux_field * d.in_fstride;
@@ -1133,64 +1153,119 @@ cfd_status build_biased(cfd_plan *p) {
             const int64_t entries = (int64_t)p->nfields * q.nlines;
             p->bpinfo.push_back({(int64_t)b, (int64_t)o, ev_total, entries});
             ev_total += entries;
-            const int f0 = op.field < 0 ? 0 : op.field;
-            const int nf = op.field < 0 ? p->nfields : 1;
-            // partitions: every partition keeps at least two rows ((P-1) ceil(N/P) <= N - 2)
-            const int N = q.N;
-            // (at most 12 rows per partition where 4 partitions allow it: fewer registers)
-            const int P = (N <= 12) ? 1 : (N <= 24) ? 2 : (N <= kBiasMaxPN) ? 4 : 0;
-            const int Lr = P ? (N + P - 1) / P : 0;
-            const int L = P == 0 ? 0 : (Lr <= 8 ? 8 : Lr <= 12 ? 12 : 16);
-            const int xdir = (P > 0 && op.dir == 0) ? 1 : 0;
-            const std::array<int, 3> key{q.hb, L, xdir};
-            const int step = P ? kWave * (4 / P) : kWave;
-            size_t lds = biased_lds(p->dtype != CFD_F64, q.hb, L, xdir, P ? P : 1, N);
-            size_t &cl = cls_lds[key];
-            cl = std::max(cl, lds);
-            // unit = the items of one line group over all selected fields (they share the velocity)
-            for (int l0 = 0; l0 < q.nlines; l0 += step) {
-                by_unit[key].push_back((int)by_cls[key].size());
-                for (int f = 0; f < nf; ++f) by_cls[key].push_back(BiasItem{pi, f0 + f, l0, P});
+            PassPlan w;
+            w.op = o;
+            w.cost = npts;
+            w.g.hb = q.hb;
+            w.g.emb = p->emb_sch[o] >= 0;
+            const size_t es = f32 ? 4 : 8;
+            w.g.big = (uint64_t)std::max(d.in_fstride, d.out_fstride) * es >= (uint64_t(1) << 32);
+            if (bias_split(q.N, op.dir, w.sp)) {
+                w.g.set = w.sp.set;
+                w.g.tilew = bias_tile_elems(w.sp, op.dir, q.hb, q.ng, q.periodic, q.N);
+                w.step = 4 * (kWave >> w.sp.lgP);
+                w.meta = w.sp.lgP | (w.sp.Lr << 4) | (w.sp.code << 12);
+            } else {
+                if (w.g.emb) return fail(CFD_EUNSUPPORTED, "biased operator: line too long for an embedded second derivative");
+                w.g.sweep = 1;
+                w.g.big = 0;
+                w.step = kWave;
+                w.meta = 0;
             }
+            pp.push_back(w);
         }
     }
-    // Where the device deals workgroups round-robin over its 8 XCDs, a line
-    // group's items (all its fields) go to one XCD: units are dealt to XCDs in
-    // turn and position 8 r + x holds XCD x's r-th item, queues padded with
-    // empty items, so the velocity lines stay in that XCD's L2.
-    if (p->xcd_interleave_ok) {
-        for (auto &kv : by_cls) {
-            if (kv.first[1] == 0) continue;   // sweep kernel: four items per workgroup, plain order
-            const std::vector<int> &u0 = by_unit[kv.first];
-            std::vector<std::vector<BiasItem>> q(kXCDq);
-            for (size_t ui = 0; ui < u0.size(); ++ui) {
-                const int b0 = u0[ui], b1 = (ui + 1 < u0.size()) ? u0[ui + 1] : (int)kv.second.size();
-                for (int i = b0; i < b1; ++i) q[ui % kXCDq].push_back(kv.second[i]);
+    // Items: one launch per kernel class.  Within a class the items of one
+    // block-field are adjacent, every direction's lines after each other, so
+    // they share its input in the L2, and the fields of a block follow one
+    // another, so they share the velocity.  Where the device deals workgroups
+    // round-robin over its 8 XCDs (each with an L2 of its own), (block, run of
+    // fields) units are dealt to XCD queues, largest first to the least loaded,
+    // and position 8 r + x holds queue x's r-th item (queues padded with empty
+    // items): a unit is at most 1/24 of the step, which balances the queues
+    // while the velocity is fetched for few units of a block.
+    const size_t nbops = bops.size();
+    using Key = std::array<int, 5>;
+    auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.set, g.emb, g.big}; };
+    struct Unit {
+        int b, f0, f1;
+        int64_t cost;
+    };
+    std::vector<Unit> units;
+    int64_t total = 0;
+    for (size_t b = 0; b < p->blocks.size(); ++b)
+        for (size_t i = 0; i < nbops; ++i)
+            total += pp[b * nbops + i].cost * (p->ops[bops[i]].field < 0 ? p->nfields : 1);
+    for (size_t b = 0; b < p->blocks.size(); ++b) {
+        Unit u{(int)b, 0, 0, 0};
+        for (int f = 0; f < p->nfields; ++f) {
+            int64_t c = 0;
+            for (size_t i = 0; i < nbops; ++i) {
+                const int of = p->ops[bops[i]].field;
+                if (of < 0 || of == f) c += pp[b * nbops + i].cost;
             }
-            size_t len = 0;
-            for (auto &v : q) len = std::max(len, v.size());
-            std::vector<BiasItem> inter(len * kXCDq, BiasItem{-1, 0, 0, 0});
-            for (int x = 0; x < kXCDq; ++x)
-                for (size_t r = 0; r < q[x].size(); ++r) inter[r * kXCDq + x] = q[x][r];
-            kv.second.swap(inter);
+            if (u.cost > 0 && u.cost + c > total / (3 * kXCDq)) {
+                units.push_back(u);
+                u = Unit{(int)b, f, f, 0};
+            }
+            u.cost += c;
+            u.f1 = f + 1;
         }
+        if (u.cost > 0) units.push_back(u);
+    }
+    const bool deal = p->xcd_interleave_ok;
+    std::vector<int> queue(units.size(), 0);
+    if (deal) {
+        std::vector<size_t> ord(units.size());
+        for (size_t i = 0; i < ord.size(); ++i) ord[i] = i;
+        std::stable_sort(ord.begin(), ord.end(), [&](size_t x, size_t y) { return units[x].cost > units[y].cost; });
+        std::vector<int64_t> load(kXCDq, 0);
+        for (size_t i : ord) {
+            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            queue[i] = k;
+            load[k] += units[i].cost;
+        }
+    }
+    std::map<Key, std::vector<std::vector<BiasItem>>> by_cls;
+    std::map<Key, BiasLaunch> cls;
+    for (size_t ui = 0; ui < units.size(); ++ui) {
+        const Unit &u = units[ui];
+        for (int f = u.f0; f < u.f1; ++f)
+            for (size_t i = 0; i < nbops; ++i) {
+                const size_t pi = u.b * nbops + i;
+                const PassPlan &w = pp[pi];
+                const int of = p->ops[w.op].field;
+                if (of >= 0 && of != f) continue;
+                const Key key = key_of(w.g);
+                auto &q = by_cls[key];
+                if (q.empty()) q.resize(kXCDq);
+                BiasLaunch &g = cls.emplace(key, w.g).first->second;
+                g.tilew = std::max(g.tilew, w.g.tilew);
+                for (int l0 = 0; l0 < bp[pi].nlines; l0 += w.step)
+                    q[w.g.sweep ? 0 : queue[ui]].push_back(BiasItem{(int)pi, f, l0, w.meta});
+            }
     }
     std::vector<BiasItem> items;
     for (auto &kv : by_cls) {
-        cfd_plan::BGroup g;
-        g.hb = kv.first[0];
-        g.L = kv.first[1];
-        g.xdir = kv.first[2];
-        g.lds = cls_lds[kv.first];
-        if (g.lds > p->max_lds) return fail(CFD_EUNSUPPORTED, "biased-line tile exceeds the device's LDS");
+        BiasLaunch g = cls.at(kv.first);
+        if ((size_t)4 * g.tilew * (f32 ? 4 : 8) > p->max_lds)
+            return fail(CFD_EUNSUPPORTED, "biased-line tile exceeds the device's LDS");
         g.item0 = (int64_t)items.size();
-        g.nitems = (int64_t)kv.second.size();
-        items.insert(items.end(), kv.second.begin(), kv.second.end());
+        if (deal && !g.sweep) {
+            size_t len = 0;
+            for (auto &v : kv.second) len = std::max(len, v.size());
+            for (size_t r = 0; r < len; ++r)
+                for (int k = 0; k < kXCDq; ++k)
+                    items.push_back(r < kv.second[k].size() ? kv.second[k][r] : BiasItem{-1, 0, 0, 0});
+        } else {
+            for (auto &v : kv.second) items.insert(items.end(), v.begin(), v.end());
+        }
+        if ((int64_t)items.size() > INT32_MAX) return fail(CFD_EUNSUPPORTED, "too many biased work items");
+        g.nitems = (int)((int64_t)items.size() - g.item0);
         p->bgroups.push_back(g);
     }
     p->nbitems = (int64_t)items.size();
     p->bev_entries = ev_total;
-    if (p->nbitems > INT32_MAX) return fail(CFD_EUNSUPPORTED, "too many biased work items");
     HIPCHK(dmalloc((void **)&p->d_bpass.p, bp.size() * sizeof(BiasPass)));
     HIPCHK(hipMemcpy(p->d_bpass.p, bp.data(), bp.size() * sizeof(BiasPass), hipMemcpyHostToDevice));
     HIPCHK(dmalloc((void **)&p->d_bitems.p, items.size() * sizeof(BiasItem)));
@@ -1215,11 +1290,10 @@ cfd_status launch_biased_groups(cfd_plan *p, const void *in, void *out, hipStrea
     const bool fork = p->bconcurrent && n > 1 && p->aux.size() + 1 >= n && p->ev.size() >= n;
     if (fork) HIPCHK(hipEventRecord(p->ev[0], st));
     for (size_t i = 0; i < n; ++i) {
-        const cfd_plan::BGroup &g = p->bgroups[i];
+        const BiasLaunch &g = p->bgroups[i];
         hipStream_t s = (fork && i > 0) ? p->aux[i - 1] : st;
         if (s != st) HIPCHK(hipStreamWaitEvent(s, p->ev[0], 0));
-        hipError_t e = launch_biased(p->dtype != CFD_F64, g.hb, g.L, g.xdir, g.lds,
-                                     (const BiasItem *)p->d_bitems.p + g.item0, (int)g.nitems,
+        hipError_t e = launch_biased(p->dtype != CFD_F64, g, (const BiasItem *)p->d_bitems.p + g.item0,
                                      (const BiasPass *)p->d_bpass.p, p->d_bcoef.p, in, out, ev, ends, s);
         if (e != hipSuccess) return hip_fail(e, "launching the biased-line kernel");
         if (s != st) HIPCHK(hipEventRecord(p->ev[i], s));
@@ -1351,20 +1425,12 @@ cfd_status enqueue(cfd_plan *p, const void *in, void *out, hipStream_t st) {
         if (p->nbitems > 0) return launch_biased_groups(p, in, out, st);
         return CFD_OK;
     };
-    // W operators read the second derivative stage 0 leaves in the scratch
-    const bool biased_late = !p->emb_off.empty();
-    if (!biased_late) {
-        cfd_status r = biased();
-        if (r != CFD_OK) return r;
-    }
+    cfd_status rb = biased();
+    if (rb != CFD_OK) return rb;
     // stage 0: every group reading the input; stage 1: the second stage of the
     // mixed derivatives (reads what stage 0 left in the scratch; the first
     // order stores into the output); stage 2: the second order adds to it
     for (int stage = 0; stage < 3; ++stage) {
-        if (stage == 1 && biased_late) {
-            cfd_status r = biased();
-            if (r != CFD_OK) return r;
-        }
         std::vector<const Group *> act;
         for (const Group &g : p->groups)
             if (g.nitems > 0 && !fused_iomode(g.iomode) && apply_stage(g.iomode) == stage) act.push_back(&g);
@@ -1964,69 +2030,32 @@ cfd_status cfd_plan_create(const cfd_plan_desc *desc, cfd_plan **out) {
                 ++p->n_mixed;
             }
         }
-        // W operators: their embedded (2)P1_M along the operator's direction over
-        // the block interior, into scratch (lines through the interior only)
+        // W operators: the lines their embedded (2)P1_M runs along
         for (size_t b = 0; b < p->blocks.size(); ++b) {
             const cfd_block &bl = p->blocks[b];
-            const int64_t ng = bl.ng;
-            const int64_t n[3] = {bl.n[0], bl.n[1], bl.n[2]};
-            const int64_t PX = n[0] + 2 * ng, PY = n[1] + 2 * ng, PZ = n[2] + 2 * ng;
-            const int64_t s_in[3] = {1, PX, PX * PY};
-            const int64_t s_int[3] = {1, n[0], n[0] * n[1]};
-            const int64_t npts = n[0] * n[1] * n[2];
             for (size_t o = 0; o < p->ops.size(); ++o) {
                 if (p->emb_sch[o] < 0) continue;
-                const cfd_op &op = p->ops[o];
                 const Scheme &e2 = p->schemes[p->emb_sch[o]];
-                const int nf = op.field < 0 ? p->nfields : 1, f0 = op.field < 0 ? 0 : op.field;
-                const int ld = op.dir;
-                const int u = (ld == 0) ? 1 : 0, v = (ld == 2) ? 1 : 2;
+                const int ld = p->ops[o].dir, N = bl.n[ld];
                 const bool per = bl.boundary[ld] == CFD_BOUNDARY_PERIODIC;
-                if (!per && n[ld] < 3)
+                if (!per && N < 3)
                     return fail(CFD_ESHAPE, "W operator: closure lines need at least 3 nodes for the embedded "
                                             "second derivative");
-                if (per && n[ld] < std::max(2 * e2.nl + 1, std::max(e2.m, e2.mc)))
+                if (per && N < std::max(2 * e2.nl + 1, std::max(e2.m, e2.mc)))
                     return fail(CFD_ESHAPE, "W operator: periodic line shorter than the embedded stencil");
-                const int64_t S0 = scr;
-                scr += nf * npts;
-                p->emb_off[std::make_pair((int)b, (int)o)] = S0;
                 PassHost ps;
                 ps.block = (int)b;
                 ps.dir = ld;
-                ps.field0 = f0;
-                ps.nfield = nf;
-                ps.N = (int)n[ld];
+                ps.N = N;
                 ps.ng = bl.ng;
                 ps.periodic = per;
                 ps.nl = e2.nl;
                 ps.nops = 1;
-                ps.op[0] = (int)o;
                 ps.sch[0] = p->emb_sch[o];
                 ps.par = 0;
                 ps.mi = e2.m;
                 ps.hw = std::max(e2.m, per ? 0 : e2.mc);
-                ps.iomode = 1;
-                ps.custom = true;
-                PassDesc &q = ps.geom;
-                std::memset(&q, 0, sizeof q);
-                q.in_base = p->in_off[b] + ng * (s_in[0] + s_in[1] + s_in[2]);
-                q.in_fstride = PX * PY * PZ;
-                q.su = (int32_t)s_in[u];
-                q.sv = (int32_t)s_in[v];
-                q.sd = (int32_t)s_in[ld];
-                q.out_base[0] = S0;
-                q.out_fstride = npts;
-                q.osu = (int32_t)s_int[u];
-                q.osv = (int32_t)s_int[v];
-                q.osd = (int32_t)s_int[ld];
-                q.nu = (int32_t)n[u];
-                q.nlines = (int32_t)(n[u] * n[v]);
-                q.field0 = f0;
-                q.N = ps.N;
-                q.ng = ps.ng;
-                q.periodic = per;
-                q.nfield_pass = nf;
-                p->passes.push_back(ps);
+                p->emb_lines.push_back(ps);
             }
         }
         p->mscr_elems = scr;
@@ -2185,6 +2214,13 @@ cfd_status cfd_plan_set_schedule(cfd_plan *p, int N, int xlines, int partitions,
             bool any = false;
             for (const PassHost &ps : p->passes) {
                 if (ps.N != N || (ps.dir == 0) != (xlines != 0) || fused_pass(ps)) continue;
+                std::vector<int> c = candidate_Ps(ps, p->dtype != CFD_F64, p->max_lds);
+                if (std::find(c.begin(), c.end(), partitions) == c.end())
+                    return fail(CFD_EINVAL, "cfd_plan_set_schedule: no compiled kernel for that partition count");
+                any = true;
+            }
+            for (const PassHost &ps : p->emb_lines) {   // W operators: a valid choice, without effect
+                if (ps.N != N || (ps.dir == 0) != (xlines != 0)) continue;
                 std::vector<int> c = candidate_Ps(ps, p->dtype != CFD_F64, p->max_lds);
                 if (std::find(c.begin(), c.end(), partitions) == c.end())
                     return fail(CFD_EINVAL, "cfd_plan_set_schedule: no compiled kernel for that partition count");
@@ -2747,7 +2783,7 @@ cfd_status cfd_plan_set_iteration(cfd_plan *p, int iterations, int bx, int by, i
         return fail(CFD_EUNSUPPORTED, "cfd_plan_set_iteration: not available on the dense mixed-precision path");
     if (iterations > 0 && p->n_mixed > 0)
         return fail(CFD_EUNSUPPORTED, "cfd_plan_set_iteration: the plan holds mixed derivatives");
-    if (iterations > 0 && !p->emb_off.empty())
+    if (iterations > 0 && p->has_emb())
         return fail(CFD_EUNSUPPORTED, "cfd_plan_set_iteration: the plan holds W operators (their embedded second "
                                       "derivative has no iterated closure)");
     for (size_t o = 0; o < p->ops.size() && iterations > 0; ++o)
@@ -2796,7 +2832,7 @@ cfd_status cfd_plan_set_iteration(cfd_plan *p, int iterations, int bx, int by, i
             // stencil on the first and last rows
             it[o] = base[o];
             const int N = b0.n[p->ops[o].dir];
-            if (N > kBiasMaxPN)
+            if (N > kBiasIterN)
                 return fail(CFD_EUNSUPPORTED, "cfd_plan_set_iteration: iterated biased closures need lines of at most "
                                               "64 nodes");
             int la = 0, ra = 0;

@@ -144,11 +144,17 @@ struct PassDesc {
 // (cfd_biased.hip).  mode: -1 left-biased, +1 right-biased, 0 upwind by the
 // sign of the velocity field at vel_base, 2 the mean of both biases.  Coefficient record per table
 // (elements of the plan's type): [0] alpha, [1, 12) ba_{-5..5},
-// [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [32, 32 + 65) (-alpha)^n for
-// n = 0..64.
-constexpr int kBiasRec = 128;
-constexpr int kBiasPow = 32;
-constexpr int kBiasMaxPN = 64;   // longest line of the partitioned kernel (4 partitions of 16)
+// [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [kBiasPow + n] (-alpha)^n for
+// n = 0..kBiasMaxPow; W schemes also [25] beta and [26] beta / a2 of the embedded second
+// derivative's system [a2, 1, a2] = (a2 / beta)(1 + beta S-)(1 + beta S+),
+// [kBiasSt2, + 11) its stencil, [kBiasCl2, + 11) its left closure stencil
+// (both centred, unit spacing; the right closure is the mirror image) and
+// [kBiasPow2 + n] (-beta)^n.
+constexpr int kBiasSt2 = 32, kBiasCl2 = 48;
+constexpr int kBiasPow = 64, kBiasMaxPow = 1024;   // longest line of the wave kernel
+constexpr int kBiasPow2 = kBiasPow + kBiasMaxPow + 8;
+constexpr int kBiasRec = kBiasPow2 + kBiasMaxPow + 8;
+constexpr int kBiasIterN = 64;   // longest line of iterated biased closures
 struct BiasPass {
     int64_t in_base;        // input offset of field 0, interior node (0,0,0)
     int64_t in_fstride;     // input elements per field
@@ -162,23 +168,27 @@ struct BiasPass {
     double hinv;            // 1 / h
     double wrap;            // periodic: 1 / (1 - (-alpha)^N)
     int64_t ev_base;        // iterated closures: first (field 0, line 0) entry of the pass's end values
-    // Second-derivative term of W and U schemes: the value for field f at
-    // interior node (u, v, k) is src[s2_base + f s2f + u s2u + v s2v + k s2d],
-    // src the plan scratch s2 (W: the embedded h^-2 (2)P1_M f, output strides)
-    // or, with s2_in, the input (U: the sampled f'' field, input strides, s2f =
-    // 0).  Weights in a left-biased row: w2 = ba2 h^2 on interior rows, w2c =
-    // bc2 h^2 on the closure row; the right-biased rows take -w2, -w2c.
-    // Neither: s2 = null and s2_in = 0.
-    const void *s2;
-    int64_t s2_base, s2f;
+    // Second-derivative term of W and U schemes.  U (s2_in): the sampled f'' at
+    // interior node (u, v, k) is in[s2_base + u s2u + v s2v + k s2d].  W: solved
+    // in the kernel at unit spacing; wrap2 = 1 / (1 - (-beta)^N) on periodic
+    // lines, det2 = 1 / (1 - (-beta)^(2N - 2)) on closure lines.  Weights in a
+    // left-biased row: w2 on interior rows (U: ba2 h^2, W: ba2), w2c = bc2 h^2
+    // on the closure row; the right-biased rows take -w2, -w2c.
+    int64_t s2_base;
     int32_t s2u, s2v, s2d, s2_in;
-    double w2, w2c;
+    double w2, w2c, wrap2, det2;
 };
-// One work item of the partitioned kernel: 64 * (4 / P) lines of one field of
-// one pass, P partitions per line (one wave each); of the sweep kernel (lines
-// longer than kBiasMaxPN): 64 lines per wave, P = 0.
+// One work item.  Wave kernel: 4 waves of 64 >> lgP lines of one field of one
+// pass; meta: lgP in bits 0..3, rows per partition in bits 4..11, index of the
+// partition length in the kernel's compiled set in bits 12..15.  Sweep kernel:
+// 64 lines of one wave.
 struct BiasItem {
-    int32_t pass, field, line0, P;
+    int32_t pass, field, line0, meta;
+};
+// How the wave kernel splits a line: 1 << lgP lane partitions of Lr rows;
+// kernel set and index of the compiled partition length in it.
+struct BiasSplit {
+    int lgP, Lr, set, code;
 };
 
 // One work item: 64 * (waves_for(P) / P) lines of one field of one pass.
@@ -330,17 +340,23 @@ hipError_t launch_wave_stage(int f32, const void *u0, const void *src, void *sta
 }  // namespace cfd
 
 namespace cfd {
-// biased (upwind) lines (cfd_biased.hip); hb: stencil half-width class 2..5;
-// L: partition length class of the partitioned kernel (8, 12 or 16), 0 for the
-// sweep kernel; xdir: lines along x (LDS-staged).
-// lds: bytes of dynamic LDS.
+// biased (upwind) lines (cfd_biased.hip)
 bool biased_supported(int hb);
-size_t biased_lds(int f32, int hb, int L, int xdir, int P, int N);
+// split of the lines of one pass for the wave kernel; false: the sweep kernel takes them
+bool bias_split(int N, int dir, BiasSplit &s);
+// elements of one wave's LDS tile (x lines; 0 along y and z)
+int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, int N);
+// One launch: hb: stencil half-width class 2..5; sweep, or the wave kernel's set (partition lengths), emb (embedded
+// second derivative) and big (fields of 4 GiB and more); tilew: elements of one wave's LDS tile.
+struct BiasLaunch {
+    int hb = 0, sweep = 0, set = 0, emb = 0, big = 0, tilew = 0;
+    int nitems = 0;
+    int64_t item0 = 0;
+};
 // ev: entering end values of an iterated closure (nullptr: the block closure); ends: receives every
-// line's end values (nullptr: not written); partitioned kernel only (L > 0)
-hipError_t launch_biased(int f32, int hb, int L, int xdir, size_t lds, const BiasItem *items, int nitems,
-                         const BiasPass *passes, const void *coefs, const void *in, void *out, const void *ev,
-                         void *ends, hipStream_t st);
+// line's end values (nullptr: not written); wave kernel only
+hipError_t launch_biased(int f32, const BiasLaunch &g, const BiasItem *items, const BiasPass *passes,
+                         const void *coefs, const void *in, void *out, const void *ev, void *ends, hipStream_t st);
 // recs: npass records (ev base of the pass, of its left neighbour, of its right neighbour, entries)
 hipError_t launch_bias_gather(int f32, int npass, int64_t max_entries, const int64_t *recs, const void *ends, void *ev,
                               hipStream_t st);
