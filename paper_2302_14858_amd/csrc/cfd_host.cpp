@@ -1049,18 +1049,20 @@ cfd_status build_biased(cfd_plan *p) {
         for (int m = 0; m < 2 * kBiasHalf + 1; ++m) r[1 + m] = s.ba[m];
         for (int m = 0; m < 2 * kBiasHalf + 2; ++m) r[12 + m] = s.bc[m];
         r[24] = 1.0 / (1.0 - s.balpha * s.balpha);
+        r[27] = s.balpha != 0.0 ? -1.0 / s.balpha : 0.0;
         double pw = 1.0;
         for (int n = 0; n <= kBiasMaxPow; ++n, pw *= -s.balpha) r[kBiasPow + n] = pw;
         if (p->emb_sch[bops[i]] >= 0) {
             const Scheme &e2 = p->schemes[p->emb_sch[bops[i]]];
             const double a2 = e2.lhs[kMaxNL + 1];
             const int hb = s.bhalf < 2 ? 2 : s.bhalf;
-            // the kernel's bounds: interior half-width 3, closure half-width hb + 1, one implicit neighbour
-            if (e2.nl != 1 || !(a2 > 0 && a2 < 0.5) || e2.m > 3 || e2.mc > std::min(hb + 1, kMaxHalf))
+            // the kernel's bounds: interior half-width 3, closure half-width hb, one implicit neighbour
+            if (e2.nl != 1 || !(a2 > 0 && a2 < 0.5) || e2.m > std::min(hb, 3) || e2.mc > hb || hb < 3)
                 return fail(CFD_EUNSUPPORTED, "biased operator: embedded second derivative outside the kernel's bounds");
             betas[i] = (1.0 - std::sqrt(1.0 - 4.0 * a2 * a2)) / (2.0 * a2);
             r[25] = betas[i];
             r[26] = betas[i] / a2;
+            r[28] = -1.0 / betas[i];
             for (int m = 0; m < 2 * kMaxHalf + 1; ++m) {
                 r[kBiasSt2 + m] = e2.rhs[m];
                 r[kBiasCl2 + m] = e2.cl[0][m];
@@ -1160,11 +1162,10 @@ cfd_status build_biased(cfd_plan *p) {
             w.g.emb = p->emb_sch[o] >= 0;
             const size_t es = f32 ? 4 : 8;
             w.g.big = (uint64_t)std::max(d.in_fstride, d.out_fstride) * es >= (uint64_t(1) << 32);
-            if (bias_split(q.N, op.dir, w.sp)) {
-                w.g.set = w.sp.set;
+            if (bias_split(q.N, op.dir, w.g.emb, w.sp)) {
                 w.g.tilew = bias_tile_elems(w.sp, op.dir, q.hb, q.ng, q.periodic, q.N);
                 w.step = 4 * (kWave >> w.sp.lgP);
-                w.meta = w.sp.lgP | (w.sp.Lr << 4) | (w.sp.code << 12);
+                w.meta = w.sp.lgP | (w.sp.L << 4);
             } else {
                 if (w.g.emb) return fail(CFD_EUNSUPPORTED, "biased operator: line too long for an embedded second derivative");
                 w.g.sweep = 1;
@@ -1185,8 +1186,8 @@ cfd_status build_biased(cfd_plan *p) {
     // items): a unit is at most 1/24 of the step, which balances the queues
     // while the velocity is fetched for few units of a block.
     const size_t nbops = bops.size();
-    using Key = std::array<int, 5>;
-    auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.set, g.emb, g.big}; };
+    using Key = std::array<int, 4>;
+    auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.emb, g.big}; };
     struct Unit {
         int b, f0, f1;
         int64_t cost;

@@ -144,9 +144,11 @@ struct PassDesc {
 // (cfd_biased.hip).  mode: -1 left-biased, +1 right-biased, 0 upwind by the
 // sign of the velocity field at vel_base, 2 the mean of both biases.  Coefficient record per table
 // (elements of the plan's type): [0] alpha, [1, 12) ba_{-5..5},
-// [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [kBiasPow + n] (-alpha)^n for
+// [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [27] -1 / alpha (0 for alpha =
+// 0), [kBiasPow + n] (-alpha)^n for
 // n = 0..kBiasMaxPow; W schemes also [25] beta and [26] beta / a2 of the embedded second
 // derivative's system [a2, 1, a2] = (a2 / beta)(1 + beta S-)(1 + beta S+),
+// [28] -1 / beta,
 // [kBiasSt2, + 11) its stencil, [kBiasCl2, + 11) its left closure stencil
 // (both centred, unit spacing; the right closure is the mirror image) and
 // [kBiasPow2 + n] (-beta)^n.
@@ -179,16 +181,14 @@ struct BiasPass {
     double w2, w2c, wrap2, det2;
 };
 // One work item.  Wave kernel: 4 waves of 64 >> lgP lines of one field of one
-// pass; meta: lgP in bits 0..3, rows per partition in bits 4..11, index of the
-// partition length in the kernel's compiled set in bits 12..15.  Sweep kernel:
-// 64 lines of one wave.
+// pass; meta: lgP in bits 0..3, rows per partition L in bits 4..11.  Sweep
+// kernel: 64 lines of one wave.
 struct BiasItem {
     int32_t pass, field, line0, meta;
 };
-// How the wave kernel splits a line: 1 << lgP lane partitions of Lr rows;
-// kernel set and index of the compiled partition length in it.
+// How the wave kernel splits a line: 1 << lgP lane partitions of L or L - 1 rows.
 struct BiasSplit {
-    int lgP, Lr, set, code;
+    int lgP, L;
 };
 
 // One work item: 64 * (waves_for(P) / P) lines of one field of one pass.
@@ -343,13 +343,13 @@ namespace cfd {
 // biased (upwind) lines (cfd_biased.hip)
 bool biased_supported(int hb);
 // split of the lines of one pass for the wave kernel; false: the sweep kernel takes them
-bool bias_split(int N, int dir, BiasSplit &s);
+bool bias_split(int N, int dir, int emb, BiasSplit &s);
 // elements of one wave's LDS tile (x lines; 0 along y and z)
 int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, int N);
-// One launch: hb: stencil half-width class 2..5; sweep, or the wave kernel's set (partition lengths), emb (embedded
-// second derivative) and big (fields of 4 GiB and more); tilew: elements of one wave's LDS tile.
+// One launch: hb: stencil half-width class 2..5; sweep, or the wave kernel's emb (embedded second derivative) and
+// big (fields of 4 GiB and more); tilew: elements of one wave's LDS tile.
 struct BiasLaunch {
-    int hb = 0, sweep = 0, set = 0, emb = 0, big = 0, tilew = 0;
+    int hb = 0, sweep = 0, emb = 0, big = 0, tilew = 0;
     int nitems = 0;
     int64_t item0 = 0;
 };
