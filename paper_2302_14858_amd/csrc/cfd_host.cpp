@@ -122,6 +122,7 @@ struct cfd_plan {
     int64_t in_elems = 0, out_elems = 0;
     std::vector<PassHost> passes;
     std::map<std::pair<int, int>, int> sched_P;   // (N, x-direction) -> partitions per line
+    bool auto_shape = true;               // launch shape by build_groups' rule, until a schedule is set or tuned
     bool persistent = true;
     bool split_x = false;                 // x-lines in a launch of their own
     bool xcd = false;                     // XCD-aware queues (persistent grid only)
@@ -326,9 +327,13 @@ int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
         Lok[n] = L;
         ++n;
     }
-    // default preference: y/z lines: fewest partitions with L <= 24 (register
-    // budget); x lines: L <= 16 (LDS tile); then the rest, most partitions first
-    const int Lcap = ps.dir == 0 ? 16 : 24;
+    // default preference: the fewest partitions of at most 16 rows (x lines 12,
+    // for the LDS tile), which the kernel classes without long partitions take:
+    // fewer registers, more waves per SIMD, and one launch where a plan's lines
+    // all have them (64 blocks of 22 fields, penta D1 + D2, FP64: 570 us; with
+    // 16 rows in x lines too 800, with up to 24 rows in y and z lines 722); then
+    // the rest, most partitions first
+    const int Lcap = ps.dir == 0 ? 12 : 16;
     int m = 0;
     for (int i = 0; i < n; ++i)
         if (Lok[i] <= Lcap) out[m++] = ok[i];
@@ -644,6 +649,38 @@ cfd_status build_groups(cfd_plan *p) {
             P = it->second;
         place_pass(ps, f32, P);
     }
+    // Short launches are latency: where passes of one kind and stage fall into
+    // several classes (their partition lengths apart, the same kernel) and all
+    // their items are no more than 16 workgroups per CU, one class with every
+    // length takes them in one launch (four blocks of 13 - 61 nodes, 5 fields,
+    // penta D1 + D2: 46 us in two launches, 36 in one; on 64 blocks of 22 fields the smaller classes'
+    // registers are worth more, 570 us against 722 with a second launch).
+    {
+        using Fam = std::tuple<int, int, int, int, int, int, int, int>;
+        auto fam_of = [](const PassHost &ps) {
+            const LineClass *k = ps.cls;
+            return Fam{k->nl, k->nops, k->par, k->mi, k->hw, k->ext, k->wg, ps.iomode};
+        };
+        std::map<Fam, std::pair<std::set<int>, int64_t>> fam;   // partition lengths, items
+        for (const PassHost &ps : p->passes) {
+            if (!ps.cls) continue;
+            auto &f = fam[fam_of(ps)];
+            f.first.insert(ps.L);
+            const cfd_block &b = p->blocks[ps.block];
+            const int64_t nlines = ps.custom ? ps.geom.nlines : (int64_t)b.n[ps.dir == 0 ? 1 : 0] * b.n[ps.dir == 2 ? 1 : 2];
+            const int per_item = kWave * (waves_for(ps.P) / ps.P);
+            f.second += (nlines + per_item - 1) / per_item * ps.nfield;
+        }
+        for (PassHost &ps : p->passes) {
+            if (!ps.cls) continue;
+            const auto &f = fam.at(fam_of(ps));
+            if (f.second > 16 * p->cus) continue;
+            const LineClass *k = find_common_class(f32, ps.cls, f.first);
+            if (!k || chunked(k) != chunked(ps.cls)) continue;
+            ps.cls = k;
+            ps.lcode = (int)(std::find(k->Ls, k->Ls + k->nL, ps.L) - k->Ls);
+        }
+    }
     // 2. tables
     std::map<TabKey, int> tabidx;
     std::vector<TabKey> keys;
@@ -840,18 +877,50 @@ cfd_status build_groups(cfd_plan *p) {
     // launches, share one XCD's L2.  Workgroup b runs on XCD b mod kXCDq.
     const int nbf = (int)(p->blocks.size() * p->nfields);
     std::vector<int> bf_queue(nbf, 0);
-    if (p->xcd) {
+    if (p->auto_shape) p->persistent = p->split_x = p->concurrent = p->xcd = false;
+    auto occupancy = [](const Group &g) {   // workgroups per CU
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, g.fn, kWave * g.wg, g.lds) != hipSuccess || nb < 1)
+            nb = 1;
+        (void)hipGetLastError();
+        return nb;
+    };
+    if (p->xcd || (p->auto_shape && p->xcd_interleave_ok)) {
         std::vector<int64_t> bf_cost(nbf, 0);
+        int64_t total = 0;
         for (size_t gi = 0; gi < groups.size(); ++gi) {
             if (fused_iomode(groups[gi].iomode)) continue;   // the fused stage's copies follow the same queues
-            for (size_t e = 0; e < gitems[gi].size(); ++e) bf_cost[gbf[gi][e]] += gcost[gi][e];
+            for (size_t e = 0; e < gitems[gi].size(); ++e) {
+                bf_cost[gbf[gi][e]] += gcost[gi][e];
+                total += gcost[gi][e];
+            }
         }
         std::vector<int64_t> load(kXCDq, 0);
-        for (int bf = 0; bf < nbf; ++bf) {
-            if (!bf_cost[bf]) continue;
+        std::vector<int> ord;
+        for (int bf = 0; bf < nbf; ++bf)
+            if (bf_cost[bf]) ord.push_back(bf);
+        std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return bf_cost[x] > bf_cost[y]; });
+        for (int bf : ord) {
             const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
             bf_queue[bf] = k;
             load[k] += bf_cost[bf];
+        }
+        // Default launch shape: one workgroup per item in XCD-interleaved order
+        // if no queue holds more than 1.3 times the mean, else in plain order,
+        // on the persistent grid if that leaves it at least a quarter of a second
+        // round (64 blocks of 22 fields, penta D1 + D2, FP32: 313 us against 423;
+        // the wave operators of one 192^3 block, whose fields are too few for
+        // the 8 queues: 507 us in XCD order, 163 with one workgroup per item in
+        // plain order, 152 on the persistent grid; four blocks of 13 - 61 nodes,
+        // 5 fields, 1.04 rounds: 29.5, 31.1 and 37.6 us).
+        if (p->auto_shape) p->xcd = *std::max_element(load.begin(), load.end()) * kXCDq * 10 <= total * 13;
+    }
+    if (p->auto_shape && !p->xcd) {
+        p->persistent = true;
+        for (size_t gi = 0; gi < groups.size(); ++gi) {
+            if (fused_iomode(groups[gi].iomode)) continue;
+            const int64_t grid = (int64_t)occupancy(groups[gi]) * p->cus, n = (int64_t)gitems[gi].size();
+            if (n > grid && 4 * n < 5 * grid) p->persistent = false;
         }
     }
     std::vector<WorkItem> items;
@@ -860,10 +929,7 @@ cfd_status build_groups(cfd_plan *p) {
         Group &g = groups[gi];
         g.item0 = (int64_t)items.size();
         g.nitems = (int64_t)gitems[gi].size();
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, g.fn, kWave * g.wg, g.lds) != hipSuccess || nb < 1)
-            nb = 1;
-        (void)hipGetLastError();
+        const int nb = occupancy(g);
         g.grid_persist = (int)std::min<int64_t>(g.nitems, (int64_t)nb * p->cus);
         g.qoff_index = -1;
         if (p->xcd && g.nitems >= 8 * kXCDq && (p->persistent || p->xcd_interleave_ok)) {
@@ -1875,7 +1941,8 @@ cfd_status cfd_plan_create(const cfd_plan_desc *desc, cfd_plan **out) {
     // lines along i alone and D_j on those along j, both on the block extended
     // by its ghost layers along the other, so in either order the value at a node
     // is the same sum over the same samples, sum_a sum_b D_i[., a] D_j[., b] f[a, b],
-    // and one order is computed (64 blocks, 22 fields, three pairs, FP64: MIXED_T).
+    // and one order is computed (64 blocks, 22 fields,
+    // dissipation and three pairs, FP64: 2283 us with both orders, 1385 with one).
     // Its inner direction dj and outer di need D_dj f on the block extended by
     // its ghost layers along di (none if di is periodic).  One first-stage pass
     // D_dj f -> scratch S_dj per (block, fields, dj, scheme) covers every operator
@@ -2246,6 +2313,7 @@ cfd_status cfd_plan_set_schedule(cfd_plan *p, int N, int xlines, int partitions,
     if ((flags & CFD_SCHED_XCD) && !(flags & CFD_SCHED_PERSISTENT) && !p->xcd_interleave_ok && p->dtype != CFD_MIXED_BF16)
         return fail(CFD_EUNSUPPORTED, "cfd_plan_set_schedule: the XCD-interleaved per-item order needs workgroups "
                                       "dealt round-robin over 8 XCDs, which this device did not show");
+    p->auto_shape = false;
     p->persistent = (flags & CFD_SCHED_PERSISTENT) != 0;
     p->split_x = (flags & CFD_SCHED_SPLIT_X) != 0;
     p->xcd = (flags & CFD_SCHED_XCD) != 0;
@@ -2327,6 +2395,7 @@ cfd_status cfd_plan_autotune(cfd_plan *p, const void *in_dev, void *out_dev, voi
         p->persistent = bp;
         return r;
     }
+    p->auto_shape = false;
     // one class per (line length, x or y/z, band, fused operators)
     std::map<std::tuple<int, int, int, int>, std::vector<int>> classes;
     for (const PassHost &ps : p->passes)
@@ -2405,10 +2474,8 @@ cfd_status cfd_plan_autotune(cfd_plan *p, const void *in_dev, void *out_dev, voi
         p->concurrent = bc;
         return r;
     };
-    // Partition presets: the default preference, and a compact one (the
-    // fewest partitions with at most 16 rows for y/z lines and 12 for x
-    // lines), under which every pass can use the kernel classes compiled
-    // without long partitions (fewer registers, more waves per SIMD).  Tuning
+    // Partition presets: the default preference (at most 16 rows for y/z lines
+    // and 12 for x lines), and one with longer partitions (24 and 16).  Tuning
     // one class at a time does not find the compact set: moving a single
     // class to another kernel adds a launch.
     auto apply_preset = [&](int which) {
@@ -2418,7 +2485,7 @@ cfd_status cfd_plan_autotune(cfd_plan *p, const void *in_dev, void *out_dev, voi
             if (fused_pass(ps)) continue;
             int c[4];
             const int n = candidate_Ps(ps, f32, p->max_lds, c);
-            const int cap = ps.dir == 0 ? 12 : 16;
+            const int cap = ps.dir == 0 ? 16 : 24;
             int pick = 0;
             for (int i = 0; i < n; ++i)
                 if (partition_length(ps, f32, c[i]) <= cap && (!pick || c[i] < pick)) pick = c[i];

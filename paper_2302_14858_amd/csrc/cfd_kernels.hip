@@ -280,6 +280,19 @@ const LineClass *find_line_class(int f32, int nl, int nops, int par, int mi, int
     return best;
 }
 
+const LineClass *find_common_class(int f32, const LineClass *like, const std::set<int> &Ls) {
+    const LineClass *best = nullptr;
+    for_each_class(f32, [&](const LineClass &k) {
+        if (k.nl != like->nl || k.nops != like->nops || k.par != like->par || k.mi != like->mi || k.hw != like->hw ||
+            k.ext != like->ext || k.wg != like->wg || (best && best->nL <= k.nL))
+            return;
+        for (int L : Ls)
+            if (std::find(k.Ls, k.Ls + k.nL, L) == k.Ls + k.nL) return;
+        best = &k;
+    });
+    return best;
+}
+
 int line_class_Ls(int f32, int nl, int nops, int par, int mi, int hw, int *Ls, int cap, int ext, int wg) {
     int cnt = 0;
     for_each_class(f32, [&](const LineClass &k) {

@@ -5,6 +5,8 @@
 // partition lengths L chosen per work item.
 #pragma once
 
+#include <set>
+
 #include "cfd_internal.h"
 
 namespace cfd {
@@ -44,7 +46,10 @@ struct LineClass {
     /* tridiagonal, first + second derivative, RHS half-width 3, closures 4 */    \
     CFD_LC(T, 1, 2, 1, 3, 4, 8, 12, 16),                                          \
     CFD_LC(T, 1, 2, 1, 3, 4, 8, 12, 16, 24, 32),                                  \
-    /* tridiagonal first derivative, RHS half-width 3 (short and long lines) */   \
+    /* tridiagonal first derivative, RHS half-width 3 (short and long lines);   */ \
+    /* the class with partitions of up to 16 rows takes 72 FP64 registers (6    */ \
+    /* waves per SIMD), the one with up to 32 rows 110 (4)                      */ \
+    CFD_LC(T, 1, 1, 1, 3, 4, 8, 12, 16),                                          \
     CFD_LC(T, 1, 1, 1, 3, 4, 8, 12, 16, 24, 32),                                  \
     CFD_LC(T, 1, 1, 1, 3, 4, 48, 64),                                             \
     /* tridiagonal second derivative alone, RHS half-width up to 3 (short and   */ \
@@ -74,6 +79,7 @@ struct LineClass {
 #define CFD_LINE_CLASSES_EXT(T, F32)                                              \
     /* iterated closures of tridiagonal schemes (hybrid closure iteration) */    \
     CFD_LC_EXT(T, 1, 2, 1, 3, 4, 8, 12, 16),                                      \
+    CFD_LC_EXT(T, 1, 1, 1, 3, 4, 8, 12, 16),                                      \
     CFD_LC_EXT(T, 1, 1, 1, 3, 4, 8, 12, 16, 24, 32),                              \
     CFD_LC_EXT(T, 1, 1, 0, 5, 5, 8, 12, 16, 24, 32),                              \
     /* the fused Runge-Kutta stage of the wave system (tridiagonal first      */ \
@@ -85,6 +91,9 @@ struct LineClass {
     CFD_LC8_RK(T, 1, 1, 1, 3, 4, 16, 24, 32)
 
 const LineClass *find_line_class(int f32, int nl, int nops, int par, int mi, int hw, int L, int ext, int wg);
+// the class of like's band, operators, parities, half-widths, extension and
+// workgroup with every partition length of Ls, nullptr if there is none
+const LineClass *find_common_class(int f32, const LineClass *like, const std::set<int> &Ls);
 
 // The tables, one per precision and translation unit.
 extern const LineClass kLineClassesF64[];

@@ -339,8 +339,10 @@ __device__ __forceinline__ void store_x(T *dst, const T *tile, int nrows, int N,
     const bool second = c + 1 < ncols;
 #pragma unroll 4
     for (int r = r0; r < nrows; r += RPP) {
-        store_out(dst + (int64_t)r * N + c, tile[r * opitch + c]);
-        if (second) store_out(dst + (int64_t)r * N + c + 1, tile[r * opitch + c + 1]);
+        const T a = tile[r * opitch + c];
+        const T b = tile[r * opitch + c + 1];
+        store_out(dst + (int64_t)r * N + c, a);
+        if (second) store_out(dst + (int64_t)r * N + c + 1, b);
     }
 }
 
