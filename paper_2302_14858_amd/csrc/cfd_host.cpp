@@ -134,8 +134,8 @@ struct cfd_plan {
     // hybrid closure iteration: iterations (0: off), end-node offset c, lattice
     int iter_n = 0, iter_c = 2, lat[3] = {0, 0, 0};
     std::vector<Scheme> base_schemes;     // the block-closure schemes while schemes holds the iterated ones
-    DevBuf d_iops, d_weights, d_ends0, d_endsf, d_ebufA, d_ebufB, d_ev;
-    int n_iops = 0, iter_max_units = 0;
+    DevBuf d_iops, d_weights, d_endsf, d_ebufA, d_ebufB, d_ev;
+    int n_iops = 0, iter_max_units = 0, iter_max_x = 0;   // operators, their most lines, the longest x line
     int64_t nunits = 0;                   // 64-node interior pieces of all blocks (stage kernels)
     // device state rebuilt by build()
     DevBuf d_tab64, d_tab32, d_taboff, d_pass, d_items, d_inoff, d_qoff, d_outoff, d_shapes;
@@ -204,13 +204,12 @@ struct cfd_plan {
     void release_iteration() {
         d_iops.release();
         d_weights.release();
-        d_ends0.release();
         d_endsf.release();
         d_ebufA.release();
         d_ebufB.release();
         d_ev.release();
         n_iops = 0;
-        iter_max_units = 0;
+        iter_max_units = iter_max_x = 0;
     }
     void release() {
         drop_graph();
@@ -551,7 +550,7 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
     int maxN = 0;
     std::vector<unsigned char> recs(pops.size() * iter_op_size());
     int64_t ubase = 0;
-    int max_units = 0;
+    int max_units = 0, max_x = 0;
     for (size_t u = 0; u < pops.size(); ++u) {
         const int i = pops[u].first, o = pops[u].second;
         const PassHost &ps = p->passes[i];
@@ -581,13 +580,14 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
         pd[i].ev_base[o] = 2 * ubase;
         ubase += nunits;
         max_units = std::max(max_units, nunits);
+        if (ps.dir == 0) max_x = std::max(max_x, ps.N);
     }
     const int nw = (int)(wspecs.size() / end_weight_spec_size());
     const size_t es = p->dtype == CFD_F64 ? 8 : 4;
     HIPCHK(dmalloc((void **)&p->d_iops.p, recs.size()));
     HIPCHK(hipMemcpy(p->d_iops.p, recs.data(), recs.size(), hipMemcpyHostToDevice));
     HIPCHK(dmalloc((void **)&p->d_weights.p, std::max<int64_t>(1, wtotal) * sizeof(double)));
-    for (DevBuf *bp : {&p->d_ends0, &p->d_endsf, &p->d_ebufA, &p->d_ebufB, &p->d_ev})
+    for (DevBuf *bp : {&p->d_endsf, &p->d_ebufA, &p->d_ebufB, &p->d_ev})
         HIPCHK(dmalloc((void **)&bp->p, std::max<int64_t>(1, 2 * ubase) * es));
     {
         void *d_specs = nullptr, *d_scr = nullptr;
@@ -603,6 +603,7 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
     }
     p->n_iops = (int)pops.size();
     p->iter_max_units = max_units;
+    p->iter_max_x = max_x;
     return CFD_OK;
 }
 
@@ -1445,23 +1446,18 @@ cfd_status build(cfd_plan *p) {
     return r;
 }
 
-// Hybrid closure iteration, before the line kernels: end-node values of
-// iterate 0 and of the zero-end-value solutions, iter_n - 1 exchange steps,
-// then every line's end values for the last iterate (into d_ev).
+// Hybrid closure iteration, before the line kernels: the end values of iterate
+// 1 and the zero-end-value solutions' end-node values, then iter_n - 1 exchange
+// steps; the last one leaves every line's end values in d_ev.
 cfd_status enqueue_iteration(cfd_plan *p, const void *in, hipStream_t st) {
     const int f32 = p->dtype != CFD_F64;
-    hipError_t e = launch_end_values(f32, p->n_iops, p->iter_max_units, p->d_iops.p, (const PassDesc *)p->d_pass.p,
-                                     (const double *)p->d_weights.p, in, p->d_ends0.p, p->d_endsf.p, st);
-    const void *prev = p->d_ends0.p;
-    for (int i = 1; i < p->iter_n && e == hipSuccess; ++i) {
-        void *next = (i % 2) ? p->d_ebufA.p : p->d_ebufB.p;
+    auto buffer = [&](int i) { return i == p->iter_n ? p->d_ev.p : ((i % 2) ? p->d_ebufA.p : p->d_ebufB.p); };
+    hipError_t e = launch_end_values(f32, p->n_iops, p->iter_max_units, p->iter_max_x, p->d_iops.p,
+                                     (const PassDesc *)p->d_pass.p, (const double *)p->d_weights.p, in, buffer(1),
+                                     p->d_endsf.p, st);
+    for (int i = 2; i <= p->iter_n && e == hipSuccess; ++i)
         e = launch_iter_ends(f32, p->n_iops, p->iter_max_units, p->d_iops.p, (const double *)p->d_tab64.p,
-                             p->d_endsf.p, prev, next, 0, st);
-        prev = next;
-    }
-    if (e == hipSuccess)
-        e = launch_iter_ends(f32, p->n_iops, p->iter_max_units, p->d_iops.p, (const double *)p->d_tab64.p,
-                             p->d_endsf.p, prev, p->d_ev.p, 1, st);
+                             p->d_endsf.p, buffer(i - 1), buffer(i), st);
     if (e != hipSuccess) return hip_fail(e, "launching the closure iteration");
     return CFD_OK;
 }

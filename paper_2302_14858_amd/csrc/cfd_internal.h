@@ -366,10 +366,12 @@ void fill_end_weight_spec(void *dst, int N, int c, const Scheme &blk, const Sche
 void fill_iter_op(void *dst, int pass, int o, int nbr_m, int nbr_p, int64_t ubase, int nunits, int N, int c, int Npad,
                   int64_t wofs, int64_t gofs, double hinv);
 hipError_t launch_end_weights(int ntab, const void *specs, double *data, double *scratch, int stride, hipStream_t st);
-hipError_t launch_end_values(int f32, int nops, int max_units, const void *ops, const PassDesc *passes,
-                             const double *weights, const void *in, void *ends0, void *endsf, hipStream_t st);
+// ev0: receives the end values of iterate 1 (every line's iterate-0 end-node values, in its neighbours' slots);
+// max_N: the longest x line
+hipError_t launch_end_values(int f32, int nops, int max_units, int max_N, const void *ops, const PassDesc *passes,
+                             const double *weights, const void *in, void *ev0, void *endsf, hipStream_t st);
 hipError_t launch_iter_ends(int f32, int nops, int max_units, const void *ops, const double *tabs64, const void *endsf,
-                            const void *prev, void *next, int gather, hipStream_t st);
+                            const void *prev, void *next, hipStream_t st);
 }  // namespace cfd
 
 namespace cfd {

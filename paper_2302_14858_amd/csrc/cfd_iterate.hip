@@ -15,9 +15,8 @@
 //      closure of Eq. sch_cent_om) and the xf values there, as dot products of
 //      the line with rows of h^-d D_L^-1 D_R built once per plan
 //      (k_end_weights, FP64);
-//   2. k_iter_ends, step: the end-node values of the next iterate from the
-//      neighbours' current ones (no pass over the fields); gather: each line's
-//      two end values for the last iterate;
+//   2. k_iter_ends: the end-node values of the next iterate from the
+//      neighbours' current ones (no pass over the fields);
 //   3. the line kernel of the iterated system (EXT class), which adds
 //      e- g- + e+ g+ to its solution.
 #include <hip/hip_runtime.h>
@@ -110,62 +109,132 @@ struct IterOp {
     double hinv;
 };
 
-// Per line: iterate-0 end-node values (ends0) and the xf values (endsf).
+// End values are kept where they are read: slot 2 e of a line's entry e holds
+// its left end value (the left neighbour's value at N - c) and slot 2 e + 1 its
+// right one (the right neighbour's at c - 1), so a line's own end-node values
+// go to its neighbours' slots.
 template <typename T>
-__global__ void k_end_values(const IterOp *__restrict__ ops, const PassDesc *__restrict__ passes,
-                             const double *__restrict__ weights, const T *__restrict__ in, T *__restrict__ ends0,
-                             T *__restrict__ endsf) {
-    const IterOp op = ops[blockIdx.y];
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= op.nunits) return;
-    const PassDesc &pd = passes[op.pass];
-    const int f = u / pd.nlines;
-    const int line = u - f * pd.nlines;
-    const int lu = line % pd.nu, lv = line / pd.nu;
-    const T *src = in + pd.in_base + (int64_t)(pd.field0 + f) * pd.in_fstride + (int64_t)lv * pd.sv +
-                   (int64_t)lu * pd.su;
-    const int N = op.N;
-    const int R = kMaxHalf;
-    const int j0 = -min(R, pd.ng), j1 = N + min(R, pd.ng);   // stored nodes; weights beyond are zero
-    const double *w = weights + op.wofs;
-    const int W = N + 2 * R;
-    T s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    for (int j = j0; j < j1; ++j) {
-        const T v = src[(int64_t)j * pd.sd];
-        s0 += (T)w[j + R] * v;
-        s1 += (T)w[W + j + R] * v;
-        s2 += (T)w[2 * W + j + R] * v;
-        s3 += (T)w[3 * W + j + R] * v;
-    }
-    const T h = (T)op.hinv;
-    const int64_t e = 2 * (op.ubase + u);
-    ends0[e] = h * s0;
-    ends0[e + 1] = h * s1;
-    endsf[e] = h * s2;
-    endsf[e + 1] = h * s3;
+__device__ __forceinline__ void put_ends(const IterOp *ops, const IterOp &op, int u, T *ev, T left, T right) {
+    ev[2 * (ops[op.nbr_m].ubase + u) + 1] = left;
+    ev[2 * (ops[op.nbr_p].ubase + u)] = right;
 }
 
-// gather = 0: next = the end-node values of the next iterate; gather = 1:
-// next = each line's end values for the iterate after prev (left: the left
-// neighbour's value at N - c, right: the right neighbour's at c - 1).
+// Per line: the iterate-0 end-node values into ev0 and the xf values there into
+// endsf.  A workgroup takes 64 lines (lane = line) and cuts their nodes into
+// four runs, one per wave, so that the weights are wave-uniform (scalar loads)
+// and the loads of a line are in flight from four waves; the partial sums meet
+// in LDS.  x lines are staged through an LDS tile with contiguous loads (64
+// blocks of 32^3, 5 fields, FP64, three directions: 52 us; one lane per
+// line with the x lines read in place, 124 us).
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_end_values(const IterOp *__restrict__ ops, const PassDesc *__restrict__ passes, const double *__restrict__ weights,
+             const T *__restrict__ in, T *__restrict__ ev0, T *__restrict__ endsf) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const IterOp &op = ops[blockIdx.y];
+    const int u0 = blockIdx.x * 64;
+    if (u0 >= op.nunits) return;   // whole workgroup
+    const PassDesc &pd = passes[op.pass];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nlines = pd.nlines, N = op.N;
+    constexpr int R = kMaxHalf;
+    const int e = min(R, pd.ng);       // stored nodes -e .. N + e - 1; weights beyond are zero
+    const int Tn = N + 2 * e, tp = Tn | 1;
+    const int q = (Tn + 3) / 4;
+    const int j0 = wv * q, j1 = min(j0 + q, Tn);
+    auto line_of = [&](int u) -> int64_t {   // offset of node -e of unit u's line
+        const int f = u / nlines, line = u - f * nlines;
+        const int lv = line / pd.nu, lu = line - lv * pd.nu;
+        return pd.in_base + (int64_t)(pd.field0 + f) * pd.in_fstride + (int64_t)lv * pd.sv + (int64_t)lu * pd.su -
+               (int64_t)e * pd.sd;
+    };
+    const int u = min(u0 + lane, op.nunits - 1);
+    const int64_t mine = line_of(u);
+    T *part = (T *)smem;               // [4 waves][4 sums][64 lanes]
+    const double *w = weights + op.wofs + (R - e);
+    const int W = N + 2 * R;
+    T s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    auto add = [&](int j, T v) {
+        s0 += (T)w[j] * v;
+        s1 += (T)w[W + j] * v;
+        s2 += (T)w[2 * W + j] * v;
+        s3 += (T)w[3 * W + j] * v;
+    };
+    constexpr int B = 8;
+    if (pd.sd == 1) {
+        T *tile = part + 16 * 64;
+        int64_t *rows = (int64_t *)part;   // line offsets, until the partial sums
+        if (wv == 0) rows[lane] = mine;
+        __syncthreads();
+        const int total = 64 * Tn;
+        int r = threadIdx.x / Tn, j = threadIdx.x - r * Tn;
+        const int dr = 256 / Tn, dj = 256 - dr * Tn;
+        for (int k0 = threadIdx.x; k0 < total; k0 += 256 * B) {
+            T v[B];
+            int at[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                at[b] = -1;
+                if (k0 + 256 * b < total) {
+                    at[b] = r * tp + j;
+                    v[b] = in[rows[r] + j];
+                    r += dr;
+                    j += dj;
+                    if (j >= Tn) {
+                        j -= Tn;
+                        ++r;
+                    }
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (at[b] >= 0) tile[at[b]] = v[b];
+        }
+        __syncthreads();
+        for (int jj = j0; jj < j1; ++jj) add(jj, tile[lane * tp + jj]);
+    } else {
+        const T *src = in + mine;
+        int jj = j0;
+        for (; jj + B <= j1; jj += B) {
+            T v[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) v[b] = src[(int64_t)(jj + b) * pd.sd];
+#pragma unroll
+            for (int b = 0; b < B; ++b) add(jj + b, v[b]);
+        }
+        for (; jj < j1; ++jj) add(jj, src[(int64_t)jj * pd.sd]);
+    }
+    part[(wv * 4 + 0) * 64 + lane] = s0;
+    part[(wv * 4 + 1) * 64 + lane] = s1;
+    part[(wv * 4 + 2) * 64 + lane] = s2;
+    part[(wv * 4 + 3) * 64 + lane] = s3;
+    __syncthreads();
+    if (wv != 0 || u0 + lane >= op.nunits) return;
+    T s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        s[k] = (part[k * 64 + lane] + part[(4 + k) * 64 + lane]) + (part[(8 + k) * 64 + lane] + part[(12 + k) * 64 + lane]);
+    const T h = (T)op.hinv;
+    put_ends(ops, op, u, ev0, h * s[0], h * s[1]);
+    const int64_t en = 2 * (op.ubase + u);
+    endsf[en] = h * s[2];
+    endsf[en + 1] = h * s[3];
+}
+
+// One exchange step: every line's end-node values of the next iterate from its
+// end values (prev), into its neighbours' slots of next.
 template <typename T>
 __global__ void k_iter_ends(const IterOp *__restrict__ ops, const double *__restrict__ tabs64,
-                            const T *__restrict__ endsf, const T *__restrict__ prev, T *__restrict__ next, int gather) {
+                            const T *__restrict__ endsf, const T *__restrict__ prev, T *__restrict__ next) {
     const IterOp op = ops[blockIdx.y];
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= op.nunits) return;
     const int64_t e = 2 * (op.ubase + u);
-    const T em = prev[2 * (ops[op.nbr_m].ubase + u) + 1];
-    const T ep = prev[2 * (ops[op.nbr_p].ubase + u)];
-    if (gather) {
-        next[e] = em;
-        next[e + 1] = ep;
-        return;
-    }
+    const T em = prev[e], ep = prev[e + 1];
     const double *gm = tabs64 + op.gofs, *gp = gm + op.Npad;
     const int jl = op.c - 1, jr = op.N - op.c;
-    next[e] = endsf[e] + (T)gm[jl] * em + (T)gp[jl] * ep;
-    next[e + 1] = endsf[e + 1] + (T)gm[jr] * em + (T)gp[jr] * ep;
+    put_ends(ops, op, u, next, endsf[e] + (T)gm[jl] * em + (T)gp[jl] * ep,
+             endsf[e + 1] + (T)gm[jr] * em + (T)gp[jr] * ep);
 }
 
 size_t end_weight_spec_size() { return sizeof(EndWeightSpec); }
@@ -212,27 +281,28 @@ hipError_t launch_end_weights(int ntab, const void *specs, double *data, double 
     return hipGetLastError();
 }
 
-hipError_t launch_end_values(int f32, int nops, int max_units, const void *ops, const PassDesc *passes,
-                             const double *weights, const void *in, void *ends0, void *endsf, hipStream_t st) {
-    const dim3 grid((max_units + 255) / 256, nops);
+hipError_t launch_end_values(int f32, int nops, int max_units, int max_N, const void *ops, const PassDesc *passes,
+                             const double *weights, const void *in, void *ev0, void *endsf, hipStream_t st) {
+    const dim3 grid((max_units + 63) / 64, nops);
+    const size_t lds = (size_t)64 * (16 + ((max_N + 2 * kMaxHalf) | 1)) * (f32 ? 4 : 8);
     if (f32)
-        hipLaunchKernelGGL(k_end_values<float>, grid, dim3(256), 0, st, (const IterOp *)ops, passes, weights,
-                           (const float *)in, (float *)ends0, (float *)endsf);
+        hipLaunchKernelGGL(k_end_values<float>, grid, dim3(256), lds, st, (const IterOp *)ops, passes, weights,
+                           (const float *)in, (float *)ev0, (float *)endsf);
     else
-        hipLaunchKernelGGL(k_end_values<double>, grid, dim3(256), 0, st, (const IterOp *)ops, passes, weights,
-                           (const double *)in, (double *)ends0, (double *)endsf);
+        hipLaunchKernelGGL(k_end_values<double>, grid, dim3(256), lds, st, (const IterOp *)ops, passes, weights,
+                           (const double *)in, (double *)ev0, (double *)endsf);
     return hipGetLastError();
 }
 
 hipError_t launch_iter_ends(int f32, int nops, int max_units, const void *ops, const double *tabs64, const void *endsf,
-                            const void *prev, void *next, int gather, hipStream_t st) {
+                            const void *prev, void *next, hipStream_t st) {
     const dim3 grid((max_units + 255) / 256, nops);
     if (f32)
         hipLaunchKernelGGL(k_iter_ends<float>, grid, dim3(256), 0, st, (const IterOp *)ops, tabs64,
-                           (const float *)endsf, (const float *)prev, (float *)next, gather);
+                           (const float *)endsf, (const float *)prev, (float *)next);
     else
         hipLaunchKernelGGL(k_iter_ends<double>, grid, dim3(256), 0, st, (const IterOp *)ops, tabs64,
-                           (const double *)endsf, (const double *)prev, (double *)next, gather);
+                           (const double *)endsf, (const double *)prev, (double *)next);
     return hipGetLastError();
 }
 
