@@ -256,11 +256,19 @@ bool biased_supported(int hb) { return hb >= 2 && hb <= 5; }
 // wave their accesses cover less than 32 contiguous bytes, and the sweep
 // kernel, 64 lines per wave, takes over (not with an embedded second
 // derivative, which only the wave kernel solves; those lines end at 256 nodes).
+// x lines take more where that keeps a wave's rows, ghosts included, at
+// kRowPass passes or fewer.
 bool bias_split(int N, int dir, int emb, BiasSplit &s) {
     if (N < 2) return false;
     for (int lg = 0; lg <= (dir == 0 || emb ? 6 : 4); ++lg) {
         const int L = (N + (1 << lg) - 1) >> lg;
         if (L > 12) continue;
+        if (dir == 0) {
+            const int Tn = N + 2 * (kBiasHalf + 1);   // at most
+            const int rows = 64 >> lg, per = Tn > 32 ? 1 : Tn > 16 ? 2 : 4;
+            if ((rows + per - 1) / per * ((Tn + 63) / 64) > kRowPass) continue;
+            if (L < 2) return false;
+        }
         s.lgP = lg;
         s.L = L;
         return true;

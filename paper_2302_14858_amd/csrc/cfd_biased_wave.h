@@ -36,20 +36,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Walk of a lane over the elements e = lane, lane + 64, ... of the [lines][cols]
-// rows of a wave's x lines, in row-major order (dq = 64 / cols, dr = 64 % cols).
-struct RowWalk {
-    int r, j;
-    __device__ __forceinline__ RowWalk(int lane, int cols) : r(lane / cols), j(lane - lane / cols * cols) {}
-    __device__ __forceinline__ void next(int cols, int dq, int dr) {
-        j += dr;
-        r += dq;
-        const bool wrap = j >= cols;
-        j -= wrap ? cols : 0;
-        r += wrap ? 1 : 0;
-    }
-};
-
 // The same address, unknown to the compiler: what is read through it is not
 // loaded earlier, so wave-uniform values of the last phase do not hold scalar
 // registers (or, out of those, vector lanes) through the first; and the steps
@@ -69,39 +55,108 @@ __device__ __forceinline__ const CONST_AS P *later(const CONST_AS P *p) {
     return (const CONST_AS P *)a;
 }
 
-// Elements e = lane + 64 i of the rows [line][cols] of a wave's x lines into
-// val[i], all requested before any is used.  src: the first line's column 0;
-// lineoff: the lane's line's offset from there (lane = partition * NW + line),
-// which the other lanes fetch by shuffle; nval real lines.
-template <typename T, int M>
-__device__ __forceinline__ void load_rows(const T *src, T (&val)[M], int cols, int nval, int lineoff, int lane) {
-    const int total = nval * cols;
-    const int dq = 64 / cols, dr = 64 - dq * cols;
-    const char *sb = (const char *)src;
-    RowWalk w(lane, cols);
+// The x lines of a wave are moved row by row: a pass of the wave covers 64
+// columns of one row, or two or four rows of at most 32 or 16, and its addresses
+// take a wave-uniform step (walking the rows' elements 64 at a time took 95
+// vector instructions per output row, twice the solve).  bias_split keeps the
+// passes at kRowPass or fewer.
+constexpr int kRowPass = 16;
+struct RowMap {
+    int cols, nval, lgr;   // columns, real rows, log2 of rows per pass
+    int sub, col;          // this lane's row in a pass and column
+    int npass;
+    bool whole;            // one pass per row or more, every row real
+    __device__ __forceinline__ RowMap(int cols_, int nval_, int NW, int lane) : cols(cols_), nval(nval_) {
+        lgr = cols > 32 ? 0 : cols > 16 ? 1 : 2;
+        sub = lane >> (6 - lgr);
+        col = lane & ((64 >> lgr) - 1);
+        npass = (NW >> lgr) * ((cols + 63) >> 6);
+        whole = cols <= 64 && nval == NW && (npass & 3) == 0;
+    }
+    // Whole maps: fn(i, at): in pass i this lane's element lies at from its first
+    // one's, step from row to row.
+    template <typename U, typename Fn>
+    __device__ __forceinline__ void each(U step, Fn fn) const {
+        if (col < cols) {
+            U at = 0;
 #pragma unroll
-    for (int i = 0; i < M; ++i) {
-        val[i] = T(0);
-        if (64 * i < total) {
-            const int o = __shfl(lineoff, w.r);
-            if (64 * i + lane < total) val[i] = *(const T *)(sb + (uint32_t)(o + w.j) * (uint32_t)sizeof(T));
-            w.next(cols, dq, dr);
+            for (int i0 = 0; i0 < kRowPass; i0 += 4)
+                if (i0 < npass) {
+#pragma unroll
+                    for (int i = i0; i < i0 + 4; ++i) {
+                        fn(i, at);
+                        at += step << lgr;
+                    }
+                }
         }
     }
-}
-// ... and from val into the wave's tile (pitch cols | 1).
-template <typename T, int M>
-__device__ __forceinline__ void put_rows(T *tile, const T (&val)[M], int cols, int nval, int lane) {
-    const int pitch = cols | 1, total = nval * cols;
-    const int dq = 64 / cols, dr = 64 - dq * cols;
-    RowWalk w(lane, cols);
+    // Any map: fn(i, row, column) for the elements that exist.
+    template <typename Fn>
+    __device__ __forceinline__ void any(Fn fn) const {
+        int r = 0, c = 0;
 #pragma unroll
-    for (int i = 0; i < M; ++i)
-        if (64 * i < total) {
-            if (64 * i + lane < total) tile[w.r * pitch + w.j] = val[i];
-            w.next(cols, dq, dr);
-        }
+        for (int i = 0; i < kRowPass; ++i)
+            if (i < npass) {
+                if (c + col < cols && r + sub < nval) fn(i, r + sub, c + col);
+                const bool last = c + 64 >= cols;
+                r += last ? 1 << lgr : 0;
+                c = last ? 0 : c + 64;
+            }
+    }
+};
+// Rows from src (the first line's column 0; the first line is row u0 of its
+// plane) into val, all requested before any is used (elements that do not exist
+// stay undefined, and are not used).
+template <typename T>
+__device__ __forceinline__ void load_rows(const T *src, T (&val)[kRowPass], const RowMap &m, int u0,
+                                          const CONST_AS BiasPass &ps) {
+    const char *sb = (const char *)src;
+    constexpr uint32_t es = sizeof(T);
+    const uint32_t gap = (uint32_t)(ps.sv - ps.nu * ps.su);   // from a plane's last row to the next plane's first
+    if (m.whole && m.nval <= ps.nu) {   // at most two planes
+        const uint32_t vo = (uint32_t)(m.sub * ps.su + m.col) * es;
+        const int cross = ps.nu - u0 - m.sub;   // this lane's rows from here on lie in the second
+        int r = 0;
+        m.each((uint32_t)ps.su * es, [&](int i, uint32_t at) {
+            val[i] = *(const T *)(sb + (vo + at + (r >= cross ? gap * es : 0u)));
+            r += 1 << m.lgr;
+        });
+    } else {
+        // plane of row r: floor((u0 + r) / nu), exact in FP32 for these few rows
+        const float inv = 1.0f / (float)ps.nu;
+        m.any([&](int i, int r, int c) {
+            const uint32_t q = (uint32_t)(((float)(u0 + r) + 0.5f) * inv);
+            val[i] = *(const T *)(sb + ((uint32_t)(r * ps.su + c) + q * gap) * es);
+        });
+    }
+}
+// ... and from val into the wave's tile.
+template <typename T>
+__device__ __forceinline__ void put_rows(T *tile, const T (&val)[kRowPass], const RowMap &m, int pitch) {
+    if (m.whole) {
+        T *t = tile + m.sub * pitch + m.col;
+        m.each(pitch, [&](int i, int at) { t[at] = val[i]; });
+    } else {
+        m.any([&](int i, int r, int c) { tile[r * pitch + c] = val[i]; });
+    }
     wave_sync();
+}
+// ... and from the tile to consecutive rows of cols elements.
+template <typename T>
+__device__ __forceinline__ void drain_rows(T *dst, const T *tile, const RowMap &m, int pitch) {
+    constexpr uint32_t es = sizeof(T);
+    if (m.whole) {
+        const T *t = tile + m.sub * pitch + m.col;
+        const uint32_t vo = (uint32_t)(m.sub * m.cols + m.col) * es;
+        T val[kRowPass];
+        m.each(pitch, [&](int i, int at) { val[i] = t[at]; });
+        m.each((uint32_t)m.cols * es,
+               [&](int i, uint32_t at) { __builtin_nontemporal_store(val[i], (T *)((char *)dst + (vo + at))); });
+    } else {
+        m.any([&](int i, int r, int c) {
+            __builtin_nontemporal_store(tile[r * pitch + c], (T *)((char *)dst + (uint32_t)(r * m.cols + c) * es));
+        });
+    }
 }
 
 // One wave: NW = 64 / P lines of one field of one pass, P = 2^lgP partitions
@@ -125,8 +180,11 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int P = 1 << lgP, lgN = 6 - lgP, NW = 64 >> lgP;
     const int N = ps.N;
-    const int first = line0 + wv * NW;   // this wave's first line
+    int first = line0 + wv * NW;   // this wave's first line
     if (first >= ps.nlines) return;
+    // the last wave of a pass takes whole NW lines too, some of them also the
+    // wave's before it (both store the same values)
+    first = max(0, min(first, ps.nlines - NW));
     const int nfull = N - P * (L - 1);
     const int p = lane >> lgN, l = lane & (NW - 1);
     const bool full = p < nfull, islast = p == P - 1;
@@ -164,9 +222,10 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         const int e = periodic ? 0 : min(ps.ng, HB + 1);
         const int Tn = N + 2 * e, tp = Tn | 1;
         {
-            T raw[W + 2];   // NW (N + 2 e) <= 64 (L + 2 e) elements
-            load_rows(in + fbase - e, raw, Tn, nval, (int)lineoff, lane);
-            put_rows(tile, raw, Tn, nval, lane);
+            T raw[kRowPass];
+            const RowMap m(Tn, nval, NW, lane);
+            load_rows(in + fbase - e, raw, m, u0, ps);
+            put_rows(tile, raw, m, tp);
         }
         if (periodic) {
             const T *row = tile + l * tp;
@@ -261,19 +320,19 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         // line, so it is a forward and a backward recurrence over the line with
         // zero right side on the closure rows, whose values are then met with
         // the two homogeneous solutions (-b)^k, (-b)^(N-1-k).
-        const T beta = rec[25], kappa = rec[26], ibeta = rec[28];
+        const T beta = rec[25], ibeta = rec[28];
         const CONST_AS T *pb = rec + kBiasPow2;   // (-beta)^n
         T (&s)[L] = s2v;
         T e0 = T(0), e1 = T(0);
         {
             const CONST_AS T *st = rec + kBiasSt2;
-            constexpr int M2 = HB < 3 ? HB : 3;
+            constexpr int M2 = HB - 2;   // W_M: classes M + 2, (2)P1_M of half-width M
 #pragma unroll
             for (int i = 0; i < L; ++i) {
                 T r = st[5] * f[i + HB];
 #pragma unroll
                 for (int m = 1; m <= M2; ++m) r += st[5 + m] * (f[i + HB + m] + f[i + HB - m]);
-                s[i] = r * kappa;
+                s[i] = r;
             }
         }
         if (closed) {
@@ -321,16 +380,16 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         }
         K2 -= beta * S;
         if (!full) K2 *= ibeta;   // weights below count from row L - 1
-        const T w2 = (T)ps.w2;
 #pragma unroll
-        for (int i = 0; i < L; ++i) s[i] = w2 * (s[i] + K1 * pb[i] + K2 * pb[L - 1 - i]);
+        for (int i = 0; i < L; ++i) s[i] += K1 * pb[i] + K2 * pb[L - 1 - i];
         __builtin_amdgcn_sched_barrier(0);   // s before the biases' sides: fewer rows live at once
     }
     {
         const CONST_AS T *ac = later(rec) + 1 + kBiasHalf;
-        T a[2 * HB + 1];
+        constexpr int MI = EMB ? HB - 1 : HB;   // W_M: interior half-width M + 1
+        T a[2 * MI + 1];
 #pragma unroll
-        for (int m = -HB; m <= HB; ++m) a[m + HB] = ac[m];
+        for (int m = -MI; m <= MI; ++m) a[m + MI] = ac[m];
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             T x = T(0), y = T(0);
@@ -339,9 +398,9 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
                 y = -s2v[i];
             }
 #pragma unroll
-            for (int m = -HB; m <= HB; ++m) {
-                x += a[m + HB] * f[i + HB + m];
-                y -= a[m + HB] * f[i + HB - m];
+            for (int m = -MI; m <= MI; ++m) {
+                x += a[m + MI] * f[i + HB + m];
+                y -= a[m + MI] * f[i + HB - m];
             }
             rl[i] = x;
             rr[i] = y;
@@ -381,12 +440,12 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     }
 
     // The velocity, requested once the window is dead and before the solves and
-    // scans that its latency overlaps: rows k0 .. k0 + L - 1 of y and z lines, elements lane + 64 i
-    // of the rows of x lines (at most 64 L), put into order through the tile below.
-    T c[L];
+    // scans that its latency overlaps: rows k0 .. k0 + L - 1 of y and z lines,
+    // whole rows of x lines, put into order through the tile below.
+    T c[L < kRowPass ? kRowPass : L];
     if (mode == 0) {
         if (xdir) {
-            load_rows(in + ps.vel_base + base0, c, N, nval, (int)lineoff, lane);
+            load_rows(in + ps.vel_base + base0, c, RowMap(N, nval, NW, lane), u0, ps);
         } else {
             const char *vl = (const char *)(in + ps.vel_base + base0);
 #pragma unroll
@@ -445,7 +504,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     const T hinv = (T)pt.hinv;
     if (mode == 0) {
         if (xdir) {
-            put_rows(tile, c, N, nval, lane);
+            put_rows(tile, c, RowMap(N, nval, NW, lane), N | 1);
 #pragma unroll
             for (int i = 0; i < L; ++i) c[i] = trow[i];
         }
@@ -453,7 +512,8 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         for (int i = 0; i < L; ++i) {
             const T xL = rl[i] + pw[i + 1] * X;
             const T xR = rr[i] + pw[L - i] * Y;
-            rl[i] = fmin(c[i], (T)0) * (hinv * xR) + fmax(c[i], (T)0) * (hinv * xL);
+            const T ch = c[i] * hinv;
+            rl[i] = fmin(ch, (T)0) * xR + fmax(ch, (T)0) * xL;
         }
     } else if (mode < 0) {
 #pragma unroll
@@ -472,15 +532,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         for (int i = 0; i < L - 1; ++i) trow[i] = rl[i];
         if (full) trow[L - 1] = rl[L - 1];
         wave_sync();
-        const int total = nval * N, vp = N | 1;
-        const int dq = 64 / N, dr = 64 - dq * N;
-        T *orow = o + (int64_t)first * N;
-        RowWalk w(lane, N);
-#pragma unroll 4
-        for (int e = lane; e < total; e += 64) {
-            __builtin_nontemporal_store(tile[w.r * vp + w.j], orow + e);
-            w.next(N, dq, dr);
-        }
+        drain_rows(o + (int64_t)first * N, tile, RowMap(N, nval, NW, lane), N | 1);
     } else if (active) {
         const int64_t obase0 = (int64_t)u0 * pt.osu + (int64_t)v0 * pt.osv;
         const int64_t osdB = (int64_t)pt.osd * (int64_t)sizeof(T);
@@ -509,9 +561,9 @@ __device__ __forceinline__ void bias_dispatch(int L, const CONST_AS BiasPass *ps
 
 // Waves per SIMD the registers are held to.  FP64 with 12 rows: 128 registers
 // (4 waves) hold a pair of biases without spills; 64 blocks, 22 fields, X_2
-// pair: 477 us, with partitions of at most 8 rows and 5 waves 560 us (the halo
+// pair: 463 us, with partitions of at most 8 rows and 5 waves 560 us (the halo
 // doubles the loads).  With an embedded second derivative FP64 takes 2 waves
-// (777 us; 3 waves spill: 1331 us), FP32 4 (414 us; 3 waves 450 us).
+// (739 us; 3 waves spill: 1331 us), FP32 4 (354 us; 3 waves 390 us).
 #define BIAS_WPE(T, EMB) (sizeof(T) == 8 ? (EMB ? 2 : 4) : (EMB ? 4 : 6))
 // Work item meta: lgP in bits 0..3, L in bits 4..11.  tilew: elements of one
 // wave's tile.

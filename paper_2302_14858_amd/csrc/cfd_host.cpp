@@ -1122,16 +1122,18 @@ cfd_status build_biased(cfd_plan *p) {
             const Scheme &e2 = p->schemes[p->emb_sch[bops[i]]];
             const double a2 = e2.lhs[kMaxNL + 1];
             const int hb = s.bhalf < 2 ? 2 : s.bhalf;
-            // the kernel's bounds: interior half-width 3, closure half-width hb, one implicit neighbour
-            if (e2.nl != 1 || !(a2 > 0 && a2 < 0.5) || e2.m > std::min(hb, 3) || e2.mc > hb || hb < 3)
+            // the kernel's bounds: one implicit neighbour, half-widths hb - 2 (f''), hb - 1 (interior rows) and hb (closures)
+            int reach = 0;
+            for (int m = -kBiasHalf; m <= kBiasHalf; ++m)
+                if (s.ba[m + kBiasHalf] != 0) reach = std::max(reach, std::abs(m));
+            if (e2.nl != 1 || !(a2 > 0 && a2 < 0.5) || e2.m > hb - 2 || reach > hb - 1 || e2.mc > hb || hb < 3)
                 return fail(CFD_EUNSUPPORTED, "biased operator: embedded second derivative outside the kernel's bounds");
             betas[i] = (1.0 - std::sqrt(1.0 - 4.0 * a2 * a2)) / (2.0 * a2);
             r[25] = betas[i];
-            r[26] = betas[i] / a2;
             r[28] = -1.0 / betas[i];
-            for (int m = 0; m < 2 * kMaxHalf + 1; ++m) {
-                r[kBiasSt2 + m] = e2.rhs[m];
-                r[kBiasCl2 + m] = e2.cl[0][m];
+            for (int m = 0; m < 2 * kMaxHalf + 1; ++m) {   // times the row weight ba2; the recurrences' right side also beta / a2
+                r[kBiasSt2 + m] = s.ba2 * betas[i] / a2 * e2.rhs[m];
+                r[kBiasCl2 + m] = s.ba2 * e2.cl[0][m];
             }
             pw = 1.0;
             for (int n = 0; n <= kBiasMaxPow; ++n, pw *= -betas[i]) r[kBiasPow2 + n] = pw;
@@ -1203,7 +1205,6 @@ cfd_status build_biased(cfd_plan *p) {
             q.w2 = q.w2c = q.wrap2 = q.det2 = 0.0;
             const double h2 = bl.h[op.dir] * bl.h[op.dir];
             if (p->emb_sch[o] >= 0) {   // W: solved in the kernel at unit spacing
-                q.w2 = s.ba2;
                 q.wrap2 = 1.0 / (1.0 - std::pow(-betas[i], (double)d.N));
                 q.det2 = 1.0 / (1.0 - std::pow(betas[i], 2.0 * (d.N - 1)));
             } else if (s.hermite) {     // U: the sampled f'' field of the input

@@ -146,12 +146,11 @@ struct PassDesc {
 // (elements of the plan's type): [0] alpha, [1, 12) ba_{-5..5},
 // [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [27] -1 / alpha (0 for alpha =
 // 0), [kBiasPow + n] (-alpha)^n for
-// n = 0..kBiasMaxPow; W schemes also [25] beta and [26] beta / a2 of the embedded second
+// n = 0..kBiasMaxPow; W schemes also [25] beta of the embedded second
 // derivative's system [a2, 1, a2] = (a2 / beta)(1 + beta S-)(1 + beta S+),
-// [28] -1 / beta,
-// [kBiasSt2, + 11) its stencil, [kBiasCl2, + 11) its left closure stencil
-// (both centred, unit spacing; the right closure is the mirror image) and
-// [kBiasPow2 + n] (-beta)^n.
+// [28] -1 / beta, [kBiasSt2, + 11) its stencil times ba2 beta / a2,
+// [kBiasCl2, + 11) its left closure stencil times ba2 (both centred, unit
+// spacing; the right closure is the mirror image) and [kBiasPow2 + n] (-beta)^n.
 constexpr int kBiasSt2 = 32, kBiasCl2 = 48;
 constexpr int kBiasPow = 64, kBiasMaxPow = 1024;   // longest line of the wave kernel
 constexpr int kBiasPow2 = kBiasPow + kBiasMaxPow + 8;
@@ -174,7 +173,7 @@ struct BiasPass {
     // interior node (u, v, k) is in[s2_base + u s2u + v s2v + k s2d].  W: solved
     // in the kernel at unit spacing; wrap2 = 1 / (1 - (-beta)^N) on periodic
     // lines, det2 = 1 / (1 - (-beta)^(2N - 2)) on closure lines.  Weights in a
-    // left-biased row: w2 on interior rows (U: ba2 h^2, W: ba2), w2c = bc2 h^2
+    // left-biased row: w2 on interior rows (U: ba2 h^2; W: in the table), w2c = bc2 h^2
     // on the closure row; the right-biased rows take -w2, -w2c.
     int64_t s2_base;
     int32_t s2u, s2v, s2d, s2_in;
