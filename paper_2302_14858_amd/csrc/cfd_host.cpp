@@ -169,8 +169,9 @@ struct cfd_plan {
     std::vector<hipEvent_t> ev;           // fork event, then one join event per aux stream
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    const void *eager_in = nullptr;       // capture fallback: the buffers replayed eagerly
+    const void *eager_in = nullptr;       // the captured buffers, for replays as plain launches
     void *eager_out = nullptr;
+    bool direct = false;                  // few launches: replayed as plain launches rather than as a graph
     DevBuf d_count;                       // counter of cfd_plan_count_nonfinite
     // fused wave stage: the wave operators once more as passes of iomode 3 / 4
     // with stage epilogues (EpiDesc per pass); ok once their kernels exist
@@ -193,6 +194,7 @@ struct cfd_plan {
         graph = nullptr;
         eager_in = nullptr;
         eager_out = nullptr;
+        direct = false;
     }
     // kept across rebuilds of the launch groups (autotuning, schedules)
     void release_biased_iteration() {
@@ -2244,13 +2246,25 @@ cfd_status cfd_plan_capture_graph(cfd_plan *p, const void *in_dev, void *out_dev
     p->graph = g;
     e = hipGraphInstantiate(&p->gexec, g, nullptr, nullptr, 0);
     if (e != hipSuccess) return fall_back();
+    // A graph launch costs the host about 16 us whatever it holds, a plain launch
+    // 1 - 2 us: a graph of up to kDirectNodes nodes is replayed as plain launches
+    // on the captured buffers (one 16^3 block: 16.7 us per replay as a graph, 5.8
+    // as a launch).  Any change of the plan's launches drops the graph.
+    constexpr size_t kDirectNodes = 4;
+    size_t nodes = 0;
+    if (hipGraphGetNodes(g, nullptr, &nodes) == hipSuccess && nodes <= kDirectNodes && !p->concurrent && !p->bconcurrent) {
+        p->direct = true;
+        p->eager_in = in_dev;
+        p->eager_out = out_dev;
+    }
+    (void)hipGetLastError();
     return CFD_OK;
 }
 
 cfd_status cfd_plan_launch_graph(cfd_plan *p, void *stream) {
     if (!p) return fail(CFD_EINVAL, "cfd_plan_launch_graph: null plan");
     HIPCHK(hipSetDevice(p->device));
-    if (!p->gexec) {
+    if (!p->gexec || p->direct) {
         if (p->eager_in) return enqueue(p, p->eager_in, p->eager_out, (hipStream_t)stream);
         return fail(CFD_EINVAL, "cfd_plan_launch_graph: no graph captured");
     }
