@@ -1252,8 +1252,9 @@ cfd_status build_biased(cfd_plan *p) {
     // round-robin over its 8 XCDs (each with an L2 of its own), (block, run of
     // fields) units are dealt to XCD queues, largest first to the least loaded,
     // and position 8 r + x holds queue x's r-th item (queues padded with empty
-    // items): a unit is at most 1/24 of the step, which balances the queues
-    // while the velocity is fetched for few units of a block.
+    // items): a unit is at most 1/256 of the step (one field of the larger
+    // blocks), which balances the queues; the velocity comes from the last-level
+    // cache (64 blocks, 22 fields, X_2 pair, FP64: 454 us; units of 1/24 463).
     const size_t nbops = bops.size();
     using Key = std::array<int, 4>;
     auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.emb, g.big}; };
@@ -1274,7 +1275,7 @@ cfd_status build_biased(cfd_plan *p) {
                 const int of = p->ops[bops[i]].field;
                 if (of < 0 || of == f) c += pp[b * nbops + i].cost;
             }
-            if (u.cost > 0 && u.cost + c > total / (3 * kXCDq)) {
+            if (u.cost > 0 && u.cost + c > total / (32 * kXCDq)) {
                 units.push_back(u);
                 u = Unit{(int)b, f, f, 0};
             }
