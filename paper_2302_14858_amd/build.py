@@ -20,7 +20,7 @@ BUILD = os.path.join(HERE, "_build")
 
 SOURCES = ["scheme_design.cpp", "cfd_host.cpp", "cfd_kernels.hip", "cfd_kernels_f32.hip", "cfd_kernels_ext.hip",
            "cfd_kernels_ext_f32.hip", "cfd_aux.hip", "cfd_dense.hip", "cfd_noalloc.hip", "cfd_iterate.hip",
-           "cfd_biased.hip", "cfd_biased_f32.hip"]
+           "cfd_biased.hip", "cfd_biased_f32.hip", "cfd_biased_wide.hip", "cfd_biased_wide_f32.hip"]
 
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -31,7 +31,7 @@ COMMON = [
 # A wave of the biased kernel holds its rows in arrays that unrolling turns into
 # registers.  Promoted to vectors before that, the FP32 arrays are copied whole
 # at every row guard: 253 VGPRs and 218 AGPRs instead of 70 and 0.
-EXTRA = {s: ["-mllvm", "-disable-promote-alloca-to-vector=1"] for s in ("cfd_biased.hip", "cfd_biased_f32.hip")}
+EXTRA = {s: ["-mllvm", "-disable-promote-alloca-to-vector=1"] for s in SOURCES if s.startswith("cfd_biased")}
 
 
 def hipcc() -> str:

@@ -36,7 +36,9 @@
 #include "cfd_biased_wave.h"
 
 namespace cfd {
-const void *biased_wave_fn_f32(int hb, int emb, int big);   // cfd_biased_f32.hip
+const void *biased_wave_fn_f32(int hb, int emb, int big);        // cfd_biased_f32.hip
+const void *biased_wide_fn_f64(int hb, int emb, int big);        // cfd_biased_wide.hip
+const void *biased_wide_fn_f32(int hb, int emb, int big);        // cfd_biased_wide_f32.hip
 namespace {
 
 template <typename T>
@@ -325,7 +327,8 @@ hipError_t launch_biased(int f32, const BiasLaunch &g, const BiasItem *items, co
                                (const double *)in, (double *)out);
         return hipGetLastError();
     }
-    const void *fn = f32 ? biased_wave_fn_f32(g.hb, g.emb, g.big) : wave_fn<double>(g.hb, g.emb, g.big);
+    const void *fn = g.wide ? (f32 ? biased_wide_fn_f32 : biased_wide_fn_f64)(g.hb, g.emb, g.big)
+                            : (f32 ? biased_wave_fn_f32 : wave_fn<double, false>)(g.hb, g.emb, g.big);
     if (!fn) return hipErrorInvalidValue;
     const size_t lds = (size_t)4 * g.tilew * (f32 ? 4 : 8);
     if (f32)

@@ -21,6 +21,8 @@
 // bidiagonal recurrence of the same form.
 #pragma once
 
+#include <climits>
+
 #include <hip/hip_runtime.h>
 
 #include "cfd_internal.h"
@@ -159,6 +161,118 @@ __device__ __forceinline__ void drain_rows(T *dst, const T *tile, const RowMap &
     }
 }
 
+// Rows of more than 64 columns, in the WIDE kernels: column blocks of 64, every
+// row's first block, then every row's second, where RowMap's general walk, with
+// masks and a plane search in every pass, is what bounds them: x lines of 80
+// nodes, 5 fields of 80 x 96 x 96, X_2 pair, FP64 36.7 -> 26.5 us, FP32 33.0 -> 18.0
+// (96 nodes: 37.6 -> 28.2, 33.1 -> 18.5).  They are kernels of their own: in one
+// kernel the second form of the row moves costs rows of one block up to a tenth.
+struct WideMap {
+    int cols, nval, lgr;   // columns, real rows, log2 of rows per pass
+    int sub, col;          // this lane's row in a pass and column
+    int npass;
+    int lgg;               // log2 of a column block's passes / 4
+    bool whole;            // passes in groups of four, every row real, loaded from at most two planes (put_rows
+                           // stores every lane's value, so load_rows must have loaded it)
+    __device__ __forceinline__ WideMap(int cols_, int nval_, int NW, int lane, int nu) : cols(cols_), nval(nval_) {
+        lgr = cols > 32 ? 0 : cols > 16 ? 1 : 2;
+        sub = lane >> (6 - lgr);
+        col = lane & ((64 >> lgr) - 1);
+        npass = (NW >> lgr) * ((cols + 63) >> 6);
+        const int rp = NW >> lgr;   // passes of a column block
+        lgg = rp >= 16 ? 2 : rp >= 8 ? 1 : 0;
+        whole = nval == NW && rp >= 4 && nval <= nu;
+    }
+    // Whole maps: fn(i, r, at): in pass i this lane's element lies r rows below
+    // its first one and at (rows of step, columns of unit) from the first row's
+    // first.  Lanes past the last column take that column once more:
+    // they load and store what its own lane does, and no pass is masked.
+    template <typename U, typename Fn>
+    __device__ __forceinline__ void each(U step, U unit, Fn fn) const {
+#pragma unroll
+        for (int g = 0; g < kRowPass / 4; ++g)
+            if (4 * g < npass) {
+                const int blk = g >> lgg, r0 = ((g - (blk << lgg)) << 2) << lgr;
+                const U c = (U)sub * step + (U)min(col + 64 * blk, cols - 1) * unit;
+                U at = (U)r0 * step;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    fn(4 * g + i, r0 + (i << lgr), c + at);
+                    at += step << lgr;
+                }
+            }
+    }
+    // Any map: fn(i, row, column) for the elements that exist.
+    template <typename Fn>
+    __device__ __forceinline__ void any(Fn fn) const {
+        int r = 0, c = 0;
+#pragma unroll
+        for (int i = 0; i < kRowPass; ++i)
+            if (i < npass) {
+                if (c + col < cols && r + sub < nval) fn(i, r + sub, c + col);
+                const bool last = c + 64 >= cols;
+                r += last ? 1 << lgr : 0;
+                c = last ? 0 : c + 64;
+            }
+    }
+};
+// Rows from src (the first line's column 0; the first line is row u0 of its
+// plane) into val, all requested before any is used (elements that do not exist
+// stay undefined, and are not used).
+template <typename T>
+__device__ __forceinline__ void load_rows(const T *src, T (&val)[kRowPass], const WideMap &m, int u0,
+                                          const CONST_AS BiasPass &ps) {
+    const char *sb = (const char *)src;
+    constexpr uint32_t es = sizeof(T);
+    const uint32_t gap = (uint32_t)(ps.sv - ps.nu * ps.su);   // from a plane's last row to the next plane's first
+    if (m.whole && m.nval <= ps.nu) {   // at most two planes
+        const int cross = ps.nu - u0 - m.sub;   // this lane's rows from here on lie in the second
+        m.each((uint32_t)ps.su * es, es, [&](int i, int r, uint32_t at) {
+            val[i] = *(const T *)(sb + (at + (r >= cross ? gap * es : 0u)));
+        });
+    } else {
+        // plane of row r: floor((u0 + r) / nu), exact in FP32 for these few rows
+        const float inv = 1.0f / (float)ps.nu;
+        m.any([&](int i, int r, int c) {
+            const uint32_t q = (uint32_t)(((float)(u0 + r) + 0.5f) * inv);
+            val[i] = *(const T *)(sb + ((uint32_t)(r * ps.su + c) + q * gap) * es);
+        });
+    }
+}
+// ... and from val into the wave's tile.
+template <typename T>
+__device__ __forceinline__ void put_rows(T *tile, const T (&val)[kRowPass], const WideMap &m, int pitch) {
+    if (m.whole) {
+        m.each(pitch, 1, [&](int i, int, int at) { tile[at] = val[i]; });
+    } else {
+        m.any([&](int i, int r, int c) { tile[r * pitch + c] = val[i]; });
+    }
+    wave_sync();
+}
+// ... and from the tile to consecutive rows of cols elements.
+template <typename T>
+__device__ __forceinline__ void drain_rows(T *dst, const T *tile, const WideMap &m, int pitch) {
+    constexpr uint32_t es = sizeof(T);
+    if (m.whole) {
+        T val[kRowPass];
+        m.each(pitch, 1, [&](int i, int, int at) { val[i] = tile[at]; });
+        m.each((uint32_t)m.cols * es, es,
+               [&](int i, int, uint32_t at) { __builtin_nontemporal_store(val[i], (T *)((char *)dst + at)); });
+    } else {
+        m.any([&](int i, int r, int c) {
+            __builtin_nontemporal_store(tile[r * pitch + c], (T *)((char *)dst + (uint32_t)(r * m.cols + c) * es));
+        });
+    }
+}
+
+template <bool WIDE>
+__device__ __forceinline__ auto row_map(int cols, int nval, int NW, int lane, int nu) {
+    if constexpr (WIDE)
+        return WideMap(cols, nval, NW, lane, nu);
+    else
+        return RowMap(cols, nval, NW, lane);
+}
+
 // One wave: NW = 64 / P lines of one field of one pass, P = 2^lgP partitions
 // per line (lane = p NW + line).  N = P (L - 1) + nfull: the first nfull
 // partitions hold L rows, the others L - 1, so only row L - 1 differs between
@@ -170,7 +284,7 @@ __device__ __forceinline__ void drain_rows(T *dst, const T *tile, const RowMap &
 // N - 1 and the right-biased one at node 0 of every line, the values the
 // neighbours' next iterate enters with.  Off: byte offsets of a lane's line
 // relative to the wave's first line (32 bits where they fit).
-template <typename T, int HB, bool EMB, int L, typename Off>
+template <typename T, int HB, bool EMB, bool WIDE, int L, typename Off>
 __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int field, int line0, int lgP, int tilew,
                                           const T *__restrict__ coefs, const T *__restrict__ in, T *__restrict__ out,
                                           const T *__restrict__ ev, T *__restrict__ ends, T *smem) {
@@ -223,7 +337,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         const int Tn = N + 2 * e, tp = Tn | 1;
         {
             T raw[kRowPass];
-            const RowMap m(Tn, nval, NW, lane);
+            const auto m = row_map<WIDE>(Tn, nval, NW, lane, ps.nu);
             load_rows(in + fbase - e, raw, m, u0, ps);
             put_rows(tile, raw, m, tp);
         }
@@ -445,7 +559,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     T c[L < kRowPass ? kRowPass : L];
     if (mode == 0) {
         if (xdir) {
-            load_rows(in + ps.vel_base + base0, c, RowMap(N, nval, NW, lane), u0, ps);
+            load_rows(in + ps.vel_base + base0, c, row_map<WIDE>(N, nval, NW, lane, ps.nu), u0, ps);
         } else {
             const char *vl = (const char *)(in + ps.vel_base + base0);
 #pragma unroll
@@ -504,7 +618,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     const T hinv = (T)pt.hinv;
     if (mode == 0) {
         if (xdir) {
-            put_rows(tile, c, RowMap(N, nval, NW, lane), N | 1);
+            put_rows(tile, c, row_map<WIDE>(N, nval, NW, lane, pt.nu), N | 1);
 #pragma unroll
             for (int i = 0; i < L; ++i) c[i] = trow[i];
         }
@@ -532,31 +646,44 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
         for (int i = 0; i < L - 1; ++i) trow[i] = rl[i];
         if (full) trow[L - 1] = rl[L - 1];
         wave_sync();
-        drain_rows(o + (int64_t)first * N, tile, RowMap(N, nval, NW, lane), N | 1);
+        drain_rows(o + (int64_t)first * N, tile, row_map<WIDE>(N, nval, NW, lane, INT_MAX), N | 1);
     } else if (active) {
         const int64_t obase0 = (int64_t)u0 * pt.osu + (int64_t)v0 * pt.osv;
         const int64_t osdB = (int64_t)pt.osd * (int64_t)sizeof(T);
         char *dst = (char *)(o + obase0);
         const Off ovoff =
             (Off)(((int64_t)u * pt.osu + (int64_t)v * pt.osv - obase0 + (int64_t)k0 * pt.osd) * (int64_t)sizeof(T));
+        // Runs of less than 64 bytes meet their neighbours' in the L2: 97 nodes of y,
+        // 5 fields, 40.7 -> 37.2 us FP64, 34.6 -> 29.8 FP32, where shorter lines lose (48
+        // nodes, FP32: 9.0 -> 10.1).  Only in the WIDE kernels: the second store loop alone costs the
+        // narrow FP32 kernel 6 %.
+        if (!WIDE || NW * (int)sizeof(T) >= 64) {
 #pragma unroll
-        for (int i = 0; i < L - 1; ++i) {
-            __builtin_nontemporal_store(rl[i], (T *)(dst + ovoff));
-            dst = later(dst + osdB);
+            for (int i = 0; i < L - 1; ++i) {
+                __builtin_nontemporal_store(rl[i], (T *)(dst + ovoff));
+                dst = later(dst + osdB);
+            }
+            if (full) __builtin_nontemporal_store(rl[L - 1], (T *)(dst + ovoff));
+        } else {
+#pragma unroll
+            for (int i = 0; i < L - 1; ++i) {
+                *(T *)(dst + ovoff) = rl[i];
+                dst = later(dst + osdB);
+            }
+            if (full) *(T *)(dst + ovoff) = rl[L - 1];
         }
-        if (full) __builtin_nontemporal_store(rl[L - 1], (T *)(dst + ovoff));
     }
 }
 
-template <typename T, int HB, bool EMB, typename Off, int L0, int... Ls>
+template <typename T, int HB, bool EMB, bool WIDE, typename Off, int L0, int... Ls>
 __device__ __forceinline__ void bias_dispatch(int L, const CONST_AS BiasPass *ps, int field, int line0, int lgP, int tilew,
                                               const T *coefs, const T *in, T *out, const T *ev, T *ends, T *smem) {
     if (L == L0) {
-        bias_wave<T, HB, EMB, L0, Off>(ps, field, line0, lgP, tilew, coefs, in, out, ev, ends, smem);
+        bias_wave<T, HB, EMB, WIDE, L0, Off>(ps, field, line0, lgP, tilew, coefs, in, out, ev, ends, smem);
         return;
     }
     if constexpr (sizeof...(Ls) > 0)
-        bias_dispatch<T, HB, EMB, Off, Ls...>(L, ps, field, line0, lgP, tilew, coefs, in, out, ev, ends, smem);
+        bias_dispatch<T, HB, EMB, WIDE, Off, Ls...>(L, ps, field, line0, lgP, tilew, coefs, in, out, ev, ends, smem);
 }
 
 // Waves per SIMD the registers are held to.  FP64 with 12 rows: 128 registers
@@ -567,7 +694,7 @@ __device__ __forceinline__ void bias_dispatch(int L, const CONST_AS BiasPass *ps
 #define BIAS_WPE(T, EMB) (sizeof(T) == 8 ? (EMB ? 2 : 4) : (EMB ? 4 : 6))
 // Work item meta: lgP in bits 0..3, L in bits 4..11.  tilew: elements of one
 // wave's tile.
-template <typename T, int HB, bool EMB, typename Off, int... Ls>
+template <typename T, int HB, bool EMB, bool WIDE, typename Off, int... Ls>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS_WPE(T, EMB)))) void k_biased_wave(const BiasItem *__restrict__ items,
                                                      const BiasPass *__restrict__ passes,
                                                      const T *__restrict__ coefs, const T *__restrict__ in,
@@ -576,7 +703,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS_WPE(T,
     extern __shared__ __align__(16) unsigned char smem[];
     const BiasItem item = items[blockIdx.x];
     if (item.pass < 0) return;   // padding of the XCD-interleaved order (whole workgroup)
-    bias_dispatch<T, HB, EMB, Off, Ls...>(item.meta >> 4, (const CONST_AS BiasPass *)passes + item.pass, item.field, item.line0, item.meta & 15,
+    bias_dispatch<T, HB, EMB, WIDE, Off, Ls...>(item.meta >> 4, (const CONST_AS BiasPass *)passes + item.pass, item.field, item.line0, item.meta & 15,
                                           tilew, coefs, in, out, ev, ends, (T *)smem);
 }
 
@@ -585,23 +712,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS_WPE(T,
 
 // The instances of one element type: per half-width class, with or without an
 // embedded second derivative (half-widths 3 .. 5); fields of 4 GiB and more
-// (64-bit offsets) share the widest class, whose extra weights are zero.
-template <typename T>
+// (64-bit offsets) share the widest class, whose extra weights are zero, and
+// have no WIDE kernel.
+template <typename T, bool WIDE>
 const void *wave_fn(int hb, int emb, int big) {
-    if (big)
-        return emb ? (const void *)k_biased_wave<T, 5, true, uint64_t, BIAS_LS>
-                   : (const void *)k_biased_wave<T, 5, false, uint64_t, BIAS_LS>;
+    if constexpr (!WIDE)
+        if (big)
+            return emb ? (const void *)k_biased_wave<T, 5, true, false, uint64_t, BIAS_LS>
+                       : (const void *)k_biased_wave<T, 5, false, false, uint64_t, BIAS_LS>;
+    if (big) return nullptr;
     if (emb) switch (hb) {
-            case 3: return (const void *)k_biased_wave<T, 3, true, uint32_t, BIAS_LS>;
-            case 4: return (const void *)k_biased_wave<T, 4, true, uint32_t, BIAS_LS>;
-            case 5: return (const void *)k_biased_wave<T, 5, true, uint32_t, BIAS_LS>;
+            case 3: return (const void *)k_biased_wave<T, 3, true, WIDE, uint32_t, BIAS_LS>;
+            case 4: return (const void *)k_biased_wave<T, 4, true, WIDE, uint32_t, BIAS_LS>;
+            case 5: return (const void *)k_biased_wave<T, 5, true, WIDE, uint32_t, BIAS_LS>;
             default: return nullptr;
         }
     switch (hb) {
-        case 2: return (const void *)k_biased_wave<T, 2, false, uint32_t, BIAS_LS>;
-        case 3: return (const void *)k_biased_wave<T, 3, false, uint32_t, BIAS_LS>;
-        case 4: return (const void *)k_biased_wave<T, 4, false, uint32_t, BIAS_LS>;
-        case 5: return (const void *)k_biased_wave<T, 5, false, uint32_t, BIAS_LS>;
+        case 2: return (const void *)k_biased_wave<T, 2, false, WIDE, uint32_t, BIAS_LS>;
+        case 3: return (const void *)k_biased_wave<T, 3, false, WIDE, uint32_t, BIAS_LS>;
+        case 4: return (const void *)k_biased_wave<T, 4, false, WIDE, uint32_t, BIAS_LS>;
+        case 5: return (const void *)k_biased_wave<T, 5, false, WIDE, uint32_t, BIAS_LS>;
         default: return nullptr;
     }
 }

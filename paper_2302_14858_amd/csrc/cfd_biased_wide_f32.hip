@@ -1,0 +1,7 @@
+// FP32 instances of the biased wave kernel (cfd_biased_wave.h) for x lines of
+// more than 64 columns, compiled on their own so the build runs them in parallel.
+#include "cfd_biased_wave.h"
+
+namespace cfd {
+const void *biased_wide_fn_f32(int hb, int emb, int big) { return wave_fn<float, true>(hb, emb, big); }
+}  // namespace cfd

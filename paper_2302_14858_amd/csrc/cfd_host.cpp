@@ -1233,6 +1233,8 @@ cfd_status build_biased(cfd_plan *p) {
             w.g.big = (uint64_t)std::max(d.in_fstride, d.out_fstride) * es >= (uint64_t(1) << 32);
             if (bias_split(q.N, op.dir, w.g.emb, w.sp)) {
                 w.g.tilew = bias_tile_elems(w.sp, op.dir, q.hb, q.ng, q.periodic, q.N);
+                // rows moved through the tile, ghosts included, that need two column blocks
+                w.g.wide = op.dir == 0 && !w.g.big && q.N + (q.periodic ? 0 : 2 * std::min(q.ng, q.hb + 1)) > kWave;
                 w.step = 4 * (kWave >> w.sp.lgP);
                 w.meta = w.sp.lgP | (w.sp.L << 4);
             } else {
@@ -1245,6 +1247,12 @@ cfd_status build_biased(cfd_plan *p) {
             pp.push_back(w);
         }
     }
+    // One launch per stencil class: a class with wide x lines runs all its lines
+    // in the wide kernel, whose other lines cost the same within a tenth.
+    for (const PassPlan &a : pp)
+        if (a.g.wide)
+            for (PassPlan &w : pp)
+                if (!w.g.sweep && !w.g.big && w.g.hb == a.g.hb && w.g.emb == a.g.emb) w.g.wide = 1;
     // Items: one launch per kernel class.  Within a class the items of one
     // block-field are adjacent, every direction's lines after each other, so
     // they share its input in the L2, and the fields of a block follow one
@@ -1256,8 +1264,8 @@ cfd_status build_biased(cfd_plan *p) {
     // blocks), which balances the queues; the velocity comes from the last-level
     // cache (64 blocks, 22 fields, X_2 pair, FP64: 454 us; units of 1/24 463).
     const size_t nbops = bops.size();
-    using Key = std::array<int, 4>;
-    auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.emb, g.big}; };
+    using Key = std::array<int, 5>;
+    auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.emb, g.big, g.wide}; };
     struct Unit {
         int b, f0, f1;
         int64_t cost;

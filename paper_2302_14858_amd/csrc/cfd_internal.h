@@ -344,7 +344,7 @@ int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, i
 // One launch: hb: stencil half-width class 2..5; sweep, or the wave kernel's emb (embedded second derivative) and
 // big (fields of 4 GiB and more); tilew: elements of one wave's LDS tile.
 struct BiasLaunch {
-    int hb = 0, sweep = 0, emb = 0, big = 0, tilew = 0;
+    int hb = 0, sweep = 0, emb = 0, big = 0, wide = 0, tilew = 0;
     int nitems = 0;
     int64_t item0 = 0;
 };
