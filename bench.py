@@ -203,7 +203,7 @@ def extra_upwind64(steps, warmup, autotune):
     evals = wl.interior_points * wl.nfields * len(OPS_UPWIND)
     out = {"workload": "upwind64: batch64 blocks (extents from {16,24,32,48}^3, ng=5), 22 fields, beta^i d_i f "
                        "with the (1)X2 upwind pair along x,y,z, beta^i = fields 0,1,2; w2_*: the same with the "
-                       "(1)W2 pair (its embedded (2)P1_2 pass and scratch traffic are not algorithmic bytes)"}
+                       "(1)W2 pair (its embedded (2)P1_2 solve adds no bytes)"}
     refs = {}
     for label, ops, dt, es in (("f64", OPS_UPWIND, P.CFD_F64, 8), ("f32", OPS_UPWIND, P.CFD_F32, 4),
                                ("w2_f64", OPS_UPWIND_W, P.CFD_F64, 8), ("w2_f32", OPS_UPWIND_W, P.CFD_F32, 4)):

@@ -142,10 +142,9 @@ cfd_status cfd_scheme_design_biased(char family, int M, double lambda, int bias,
  * (lambda <= 0 takes the printed sigma), formal order 2M+2.  At the far end
  * k*_+ (left bias) that f'' is the closure's explicit value, which makes the
  * row there the printed Wtilde; the closure at k*_- (the printed Wbar) is
- * built as above from that explicit row.  In a plan a W operator runs the
- * (2)P1_M pass over the block interior into plan scratch before the biased
- * launches (M + 2 ghost layers; the embedded pass takes the line lengths of the
- * centred second-degree path: closure lines of 3..128 nodes, periodic lines of
+ * built as above from that explicit row.  The biased kernel solves (2)P1_M in
+ * the registers that hold the line (M + 2 ghost layers; W operators take the
+ * line lengths of the centred second-degree path: closure lines of 3..128 nodes, periodic lines of
  * P partitions of a compiled length, e.g. 8, 12, 16, 24, 32, 48, 64, 96, 128;
  * other lengths give CFD_EUNSUPPORTED at plan creation); cfd_plan_set_iteration
  * refuses plans with W operators. */
@@ -268,9 +267,9 @@ typedef struct {
  * along i (edge ghosts are read), so the outer one has its ghost values.  The
  * plan computes the inner derivatives into a scratch buffer it owns (per
  * block-field and inner direction, the block extended along the outer
- * directions the plan pairs it with; the operators of a plan share them);
- * the first order's outer derivative stores half its value into the output
- * and the second order's adds half of its own.
+ * directions the plan pairs it with; the operators of a plan share them).
+ * On a block both orders are the tensor product of the two line operators, so
+ * their mean is either of them, and one is computed.
  * aux_field: for a U_M scheme ("(1)UM-" etc., Tab. ucd_slow), which samples
  * f'' as data, the field holding the second derivative of `field` along dir
  * (read on the interior nodes; field must be a single index); -1 for every
@@ -331,7 +330,9 @@ cfd_status cfd_apply(cfd_plan *p, const void *in_dev, void *out_dev, void *strea
 cfd_status cfd_plan_capture_graph(cfd_plan *p, const void *in_dev, void *out_dev, void *stream);
 
 /* Launch the captured graph (one cfd_apply, Eq. sch_cent_om per line) on
- * `stream`.  CFD_EINVAL if none was captured.  If the runtime could not
+ * `stream`.  CFD_EINVAL if none was captured.  A captured apply of at most four
+ * launches is replayed as plain launches, which cost the host less than a graph
+ * launch (same result and status).  If the runtime could not
  * capture or instantiate the apply, cfd_plan_capture_graph kept its buffers
  * instead and this call enqueues the same apply eagerly (same result; see
  * cfd_plan_graph_status). */
@@ -423,7 +424,7 @@ void cfd_plan_destroy(cfd_plan *p);
  * iterations = 0 returns to the plain block closure.  Allocates the end-value
  * arrays (two values per line, operator and field, five arrays) and builds the
  * end-node weights in FP64 on the device; invalidates a captured graph.  An
- * apply then enqueues n + 1 small kernels over the end values before the line
+ * apply then enqueues n small kernels over the end values before the line
  * kernels, and reads the input twice.
  * Biased operators (Eq. iter_left_X and its mirror image) iterate too: for
  * i >= 1 every row of a line takes the interior scheme and the derivative at
