@@ -184,15 +184,14 @@ __global__ void k_xpcy(int64_t n, const T *__restrict__ x, T c, const T *__restr
 // that face.  Interior nodes are only read and ghost nodes only written here,
 // so stage may still alias src.
 // Bound by memory: 27 sweeps of the interior (the state read twice, the six
-// derivatives, the stage state and acc written).  Each field's loads come
-// before any store, node indices are 32-bit where they fit (a 64-bit division
-// is several dozen instructions), and what this stage alone reads, the
-// derivatives and acc_in, is loaded non-temporally, so the stage state that
-// the next derivative reads stays in the caches.  acc is stored so only where
-// rows are whole (no ghosts): partial lines lose by it.  One RK4 step, FP64:
-// 192^3 1651 -> 1628 us, 128^3 480 -> 464, 32^3 46.8 -> 44.2; a 3^3 lattice of
-// 31^3 blocks in FP32 173 -> 172 (acc non-temporal there too: 178).
-template <typename T>
+// derivatives, the stage state and acc written).  The derivatives, which this
+// stage alone reads, are loaded non-temporally, so the stage state that the
+// next derivative reads stays in the caches.  STREAM (no block has ghosts, so
+// rows are whole): every load before any store, acc streamed too.  One RK4
+// step, FP64: 192^3 1651 -> 1558 us, 128^3 479 -> 465, 32^3 46.8 -> 44.6.  With
+// ghosts it loses: on a 4^3 lattice of 17^3 blocks the stage takes 25.3 us
+// against 22.4, acc in partial lines slows a 3^3 lattice of 31^3 by 3 %.
+template <typename T, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_wave_stage(const T *u0, const T *src, T *stage, const T *acc_in, T *acc, const T *__restrict__ d,
              const int64_t *__restrict__ in_off, const int64_t *__restrict__ out_off,
@@ -232,22 +231,33 @@ k_wave_stage(const T *u0, const T *src, T *stage, const T *acc_in, T *acc, const
         auto ntl = [](const T *q) { return __builtin_nontemporal_load(q); };
         const T k[5] = {src[ip + fs], ntl(db + 3 * n3) + ntl(db + 4 * n3) + ntl(db + 5 * n3), ntl(db), ntl(db + n3),
                         ntl(db + 2 * n3)};
-        // the state pointers may alias as far as the compiler knows: a store would
-        // hold back the next field's loads
-        T nv[5], v[5], ai[5];
+        T nv[5];
+        if constexpr (STREAM) {
+            // the state pointers may alias as far as the compiler knows: a store would
+            // hold back the next field's loads
+            T v[5], ai[5];
 #pragma unroll
-        for (int f = 0; f < 5; ++f) v[f] = (stage || acc_is_u0) ? u0[ip + f * fs] : T(0);
+            for (int f = 0; f < 5; ++f) v[f] = (stage || acc_is_u0) ? u0[ip + f * fs] : T(0);
 #pragma unroll
-        for (int f = 0; f < 5; ++f) ai[f] = acc_is_u0 ? v[f] : ntl(acc_in + ip + f * fs);
+            for (int f = 0; f < 5; ++f) ai[f] = acc_is_u0 ? v[f] : ntl(acc_in + ip + f * fs);
 #pragma unroll
-        for (int f = 0; f < 5; ++f) {
-            const T sv = v[f] + a * k[f], av = ai[f] + b * k[f];
-            if (stage) stage[ip + f * fs] = sv;
-            if (ng == 0)
+            for (int f = 0; f < 5; ++f) {
+                const T sv = v[f] + a * k[f], av = ai[f] + b * k[f];
+                if (stage) stage[ip + f * fs] = sv;
                 __builtin_nontemporal_store(av, acc + ip + f * fs);
-            else
+                nv[f] = stage ? sv : av;
+            }
+        } else {
+#pragma unroll
+            for (int f = 0; f < 5; ++f) {
+                T v = T(0);
+                if (stage || acc_is_u0) v = u0[ip + f * fs];
+                const T ai = acc_is_u0 ? v : acc_in[ip + f * fs];
+                const T sv = v + a * k[f], av = ai + b * k[f];
+                if (stage) stage[ip + f * fs] = sv;
                 acc[ip + f * fs] = av;
-            nv[f] = stage ? sv : av;
+                nv[f] = stage ? sv : av;
+            }
         }
         if (bx > 0) {
             // ghost copies of this node in the neighbours across the faces it is near
@@ -343,18 +353,20 @@ namespace cfd {
 hipError_t launch_wave_stage(int f32, const void *u0, const void *src, void *stage, const void *acc_in, void *acc,
                              const void *d, const int64_t *in_off, const int64_t *out_off, const int *shapes,
                              const int *unitpre, int nblocks, int nunits, double a, double b, int bx, int by, int bz,
-                             hipStream_t st) {
+                             int stream, hipStream_t st) {
     if (nunits == 0) return hipSuccess;
     int g = (nunits + 3) / 4;
     if (g > 65535) g = 65535;
+    auto run = [&](auto kernel, auto t) {
+        using T = decltype(t);
+        hipLaunchKernelGGL(kernel, dim3(g), dim3(256), 0, st, (const T *)u0, (const T *)src, (T *)stage,
+                           (const T *)acc_in, (T *)acc, (const T *)d, in_off, out_off, shapes, unitpre, nblocks, nunits,
+                           (T)a, (T)b, bx, by, bz);
+    };
     if (f32)
-        hipLaunchKernelGGL(k_wave_stage<float>, dim3(g), dim3(256), 0, st, (const float *)u0, (const float *)src,
-                           (float *)stage, (const float *)acc_in, (float *)acc, (const float *)d, in_off, out_off,
-                           shapes, unitpre, nblocks, nunits, (float)a, (float)b, bx, by, bz);
+        stream ? run(k_wave_stage<float, true>, 0.0f) : run(k_wave_stage<float, false>, 0.0f);
     else
-        hipLaunchKernelGGL(k_wave_stage<double>, dim3(g), dim3(256), 0, st, (const double *)u0, (const double *)src,
-                           (double *)stage, (const double *)acc_in, (double *)acc, (const double *)d, in_off, out_off,
-                           shapes, unitpre, nblocks, nunits, a, b, bx, by, bz);
+        stream ? run(k_wave_stage<double, true>, 0.0) : run(k_wave_stage<double, false>, 0.0);
     return hipGetLastError();
 }
 

@@ -2791,9 +2791,10 @@ cfd_status wave_stage(cfd_plan *p, const void *u0_dev, const void *src_dev, void
     const int64_t nunits64 = p->nunits;
     if (!acc_in_dev) acc_in_dev = acc_dev;
     const int *shapes = (const int *)p->d_shapes.p;
+    const bool whole = std::all_of(p->blocks.begin(), p->blocks.end(), [](const cfd_block &q) { return q.ng == 0; });
     hipError_t e = launch_wave_stage(p->dtype == CFD_F32, u0_dev, src_dev, stage_dev, acc_in_dev, acc_dev, derivs_dev,
                                      (const int64_t *)p->d_inoff.p, (const int64_t *)p->d_outoff.p, shapes,
-                                     shapes + 4 * nb, nb, (int)nunits64, a, b, bx, by, bz, (hipStream_t)stream);
+                                     shapes + 4 * nb, nb, (int)nunits64, a, b, bx, by, bz, whole, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "launching wave stage");
     return CFD_OK;
 }

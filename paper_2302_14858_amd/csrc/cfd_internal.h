@@ -331,7 +331,7 @@ hipError_t launch_xpcy(int f32, int64_t n, const void *x, double c, const void *
 hipError_t launch_wave_stage(int f32, const void *u0, const void *src, void *stage, const void *acc_in, void *acc,
                              const void *d, const int64_t *in_off, const int64_t *out_off, const int *shapes,
                              const int *unitpre, int nblocks, int nunits, double a, double b, int bx, int by, int bz,
-                             hipStream_t st);   // bx = 0: no ghost refresh
+                             int stream, hipStream_t st);   // bx = 0: no ghost refresh
 }  // namespace cfd
 
 namespace cfd {
