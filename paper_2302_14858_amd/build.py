@@ -20,7 +20,8 @@ BUILD = os.path.join(HERE, "_build")
 
 SOURCES = ["scheme_design.cpp", "cfd_host.cpp", "cfd_kernels.hip", "cfd_kernels_f32.hip", "cfd_kernels_ext.hip",
            "cfd_kernels_ext_f32.hip", "cfd_aux.hip", "cfd_dense.hip", "cfd_noalloc.hip", "cfd_iterate.hip",
-           "cfd_biased.hip", "cfd_biased_f32.hip", "cfd_biased_wide.hip", "cfd_biased_wide_f32.hip"]
+           "cfd_biased.hip", "cfd_biased_f32.hip", "cfd_biased_wide.hip", "cfd_biased_wide_f32.hip",
+           "cfd_biased_big.hip", "cfd_biased_big_f32.hip"]
 
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

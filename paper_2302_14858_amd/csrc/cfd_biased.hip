@@ -36,9 +36,11 @@
 #include "cfd_biased_wave.h"
 
 namespace cfd {
-const void *biased_wave_fn_f32(int hb, int emb, int big);        // cfd_biased_f32.hip
-const void *biased_wide_fn_f64(int hb, int emb, int big);        // cfd_biased_wide.hip
-const void *biased_wide_fn_f32(int hb, int emb, int big);        // cfd_biased_wide_f32.hip
+const void *biased_wave_fn_f32(int hb, int emb);       // cfd_biased_f32.hip
+const void *biased_wide_fn_f64(int hb, int emb);       // cfd_biased_wide.hip
+const void *biased_wide_fn_f32(int hb, int emb);       // cfd_biased_wide_f32.hip
+const void *biased_big_fn_f64(int hb, int emb);        // cfd_biased_big.hip
+const void *biased_big_fn_f32(int hb, int emb);        // cfd_biased_big_f32.hip
 namespace {
 
 template <typename T>
@@ -251,39 +253,6 @@ const void *sweep_fn(int hb) {
 
 bool biased_supported(int hb) { return hb >= 2 && hb <= 5; }
 
-// The fewest partitions of at most 12 rows, the rows spread evenly (L or L - 1
-// per partition): fewer partitions keep the stencil halo's share of the loads
-// down, and 12 rows of a pair of biases are what fits a quarter of a SIMD's
-// registers.  y and z lines stop at 16 partitions: with fewer than 4 lines per
-// wave their accesses cover less than 32 contiguous bytes, and the sweep
-// kernel, 64 lines per wave, takes over (not with an embedded second
-// derivative, which only the wave kernel solves; those lines end at 256 nodes).
-// x lines take more where that keeps a wave's rows, ghosts included, at
-// kRowPass passes or fewer.
-bool bias_split(int N, int dir, int emb, BiasSplit &s) {
-    if (N < 2) return false;
-    for (int lg = 0; lg <= (dir == 0 || emb ? 6 : 4); ++lg) {
-        const int L = (N + (1 << lg) - 1) >> lg;
-        if (L > 12) continue;
-        if (dir == 0) {
-            const int Tn = N + 2 * (kBiasHalf + 1);   // at most
-            const int rows = 64 >> lg, per = Tn > 32 ? 1 : Tn > 16 ? 2 : 4;
-            if ((rows + per - 1) / per * ((Tn + 63) / 64) > kRowPass) continue;
-            if (L < 2) return false;
-        }
-        s.lgP = lg;
-        s.L = L;
-        return true;
-    }
-    return false;
-}
-
-int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, int N) {
-    if (dir != 0) return 0;
-    const int e = periodic ? 0 : std::min(ng, hb + 1);
-    return (64 >> s.lgP) * ((N + 2 * e) | 1) + 2;   // a partition short of a row reads one past it
-}
-
 // End values of the next iterate: for every biased pass (rec = ev base of
 // the pass, of its left neighbour along the lines, of its right neighbour,
 // entries), entry e takes the left neighbour's left-biased last value and the
@@ -327,8 +296,10 @@ hipError_t launch_biased(int f32, const BiasLaunch &g, const BiasItem *items, co
                                (const double *)in, (double *)out);
         return hipGetLastError();
     }
-    const void *fn = g.wide ? (f32 ? biased_wide_fn_f32 : biased_wide_fn_f64)(g.hb, g.emb, g.big)
-                            : (f32 ? biased_wave_fn_f32 : wave_fn<double, false>)(g.hb, g.emb, g.big);
+    const int hb = bias_instance_half(g);
+    const void *fn = g.big    ? (f32 ? biased_big_fn_f32 : biased_big_fn_f64)(hb, g.emb)
+                     : g.wide ? (f32 ? biased_wide_fn_f32 : biased_wide_fn_f64)(hb, g.emb)
+                              : (f32 ? biased_wave_fn_f32 : wave_fn<double, false, uint32_t>)(hb, g.emb);
     if (!fn) return hipErrorInvalidValue;
     const size_t lds = (size_t)4 * g.tilew * (f32 ? 4 : 8);
     if (f32)

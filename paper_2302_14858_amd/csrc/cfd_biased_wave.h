@@ -25,7 +25,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "cfd_internal.h"
+#include "cfd_biased_plan.h"
 
 namespace cfd {
 namespace {
@@ -62,7 +62,6 @@ __device__ __forceinline__ const CONST_AS P *later(const CONST_AS P *p) {
 // take a wave-uniform step (walking the rows' elements 64 at a time took 95
 // vector instructions per output row, twice the solve).  bias_split keeps the
 // passes at kRowPass or fewer.
-constexpr int kRowPass = 16;
 struct RowMap {
     int cols, nval, lgr;   // columns, real rows, log2 of rows per pass
     int sub, col;          // this lane's row in a pass and column
@@ -333,7 +332,7 @@ __device__ __forceinline__ void bias_wave(const CONST_AS BiasPass *pass, int fie
     T f[W];
     T *trow;   // x lines: this lane's rows in the tile of N columns
     if (xdir) {
-        const int e = periodic ? 0 : min(ps.ng, HB + 1);
+        const int e = bias_ghosts(ps.ng, HB, periodic);
         const int Tn = N + 2 * e, tp = Tn | 1;
         {
             T raw[kRowPass];
@@ -710,28 +709,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS_WPE(T,
 // Partition lengths compiled into every instance.
 #define BIAS_LS 12, 8, 11, 10, 9, 7, 6, 5, 4, 3, 2
 
-// The instances of one element type: per half-width class, with or without an
-// embedded second derivative (half-widths 3 .. 5); fields of 4 GiB and more
-// (64-bit offsets) share the widest class, whose extra weights are zero, and
-// have no WIDE kernel.
-template <typename T, bool WIDE>
-const void *wave_fn(int hb, int emb, int big) {
-    if constexpr (!WIDE)
-        if (big)
-            return emb ? (const void *)k_biased_wave<T, 5, true, false, uint64_t, BIAS_LS>
-                       : (const void *)k_biased_wave<T, 5, false, false, uint64_t, BIAS_LS>;
-    if (big) return nullptr;
+// The instances of one element type and row moves or offsets: per half-width
+// class, with or without an embedded second derivative (half-widths 3 .. 5).
+// Off uint64_t: fields of 4 GiB and more, which have no WIDE kernel.
+template <typename T, bool WIDE, typename Off>
+const void *wave_fn(int hb, int emb) {
     if (emb) switch (hb) {
-            case 3: return (const void *)k_biased_wave<T, 3, true, WIDE, uint32_t, BIAS_LS>;
-            case 4: return (const void *)k_biased_wave<T, 4, true, WIDE, uint32_t, BIAS_LS>;
-            case 5: return (const void *)k_biased_wave<T, 5, true, WIDE, uint32_t, BIAS_LS>;
+            case 3: return (const void *)k_biased_wave<T, 3, true, WIDE, Off, BIAS_LS>;
+            case 4: return (const void *)k_biased_wave<T, 4, true, WIDE, Off, BIAS_LS>;
+            case 5: return (const void *)k_biased_wave<T, 5, true, WIDE, Off, BIAS_LS>;
             default: return nullptr;
         }
     switch (hb) {
-        case 2: return (const void *)k_biased_wave<T, 2, false, WIDE, uint32_t, BIAS_LS>;
-        case 3: return (const void *)k_biased_wave<T, 3, false, WIDE, uint32_t, BIAS_LS>;
-        case 4: return (const void *)k_biased_wave<T, 4, false, WIDE, uint32_t, BIAS_LS>;
-        case 5: return (const void *)k_biased_wave<T, 5, false, WIDE, uint32_t, BIAS_LS>;
+        case 2: return (const void *)k_biased_wave<T, 2, false, WIDE, Off, BIAS_LS>;
+        case 3: return (const void *)k_biased_wave<T, 3, false, WIDE, Off, BIAS_LS>;
+        case 4: return (const void *)k_biased_wave<T, 4, false, WIDE, Off, BIAS_LS>;
+        case 5: return (const void *)k_biased_wave<T, 5, false, WIDE, Off, BIAS_LS>;
         default: return nullptr;
     }
 }

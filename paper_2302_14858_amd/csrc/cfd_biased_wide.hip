@@ -3,5 +3,5 @@
 #include "cfd_biased_wave.h"
 
 namespace cfd {
-const void *biased_wide_fn_f64(int hb, int emb, int big) { return wave_fn<double, true>(hb, emb, big); }
+const void *biased_wide_fn_f64(int hb, int emb) { return wave_fn<double, true, uint32_t>(hb, emb); }
 }  // namespace cfd

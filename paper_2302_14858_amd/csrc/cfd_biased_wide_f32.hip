@@ -3,5 +3,5 @@
 #include "cfd_biased_wave.h"
 
 namespace cfd {
-const void *biased_wide_fn_f32(int hb, int emb, int big) { return wave_fn<float, true>(hb, emb, big); }
+const void *biased_wide_fn_f32(int hb, int emb) { return wave_fn<float, true, uint32_t>(hb, emb); }
 }  // namespace cfd

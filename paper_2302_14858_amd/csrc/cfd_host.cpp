@@ -28,6 +28,7 @@
 #include <tuple>
 #include <vector>
 
+#include "cfd_biased_plan.h"
 #include "cfd_internal.h"
 #include "cfd_kernels_reg.h"
 
@@ -1232,9 +1233,9 @@ cfd_status build_biased(cfd_plan *p) {
             const size_t es = f32 ? 4 : 8;
             w.g.big = (uint64_t)std::max(d.in_fstride, d.out_fstride) * es >= (uint64_t(1) << 32);
             if (bias_split(q.N, op.dir, w.g.emb, w.sp)) {
-                w.g.tilew = bias_tile_elems(w.sp, op.dir, q.hb, q.ng, q.periodic, q.N);
+                w.g.tilew = bias_tile_elems(w.sp, op.dir, bias_instance_half(w.g), q.ng, q.periodic, q.N);
                 // rows moved through the tile, ghosts included, that need two column blocks
-                w.g.wide = op.dir == 0 && !w.g.big && q.N + (q.periodic ? 0 : 2 * std::min(q.ng, q.hb + 1)) > kWave;
+                w.g.wide = op.dir == 0 && !w.g.big && q.N + 2 * bias_ghosts(q.ng, q.hb, q.periodic) > kWave;
                 w.step = 4 * (kWave >> w.sp.lgP);
                 w.meta = w.sp.lgP | (w.sp.L << 4);
             } else {

@@ -337,10 +337,6 @@ hipError_t launch_wave_stage(int f32, const void *u0, const void *src, void *sta
 namespace cfd {
 // biased (upwind) lines (cfd_biased.hip)
 bool biased_supported(int hb);
-// split of the lines of one pass for the wave kernel; false: the sweep kernel takes them
-bool bias_split(int N, int dir, int emb, BiasSplit &s);
-// elements of one wave's LDS tile (x lines; 0 along y and z)
-int bias_tile_elems(const BiasSplit &s, int dir, int hb, int ng, int periodic, int N);
 // One launch: hb: stencil half-width class 2..5; sweep, or the wave kernel's emb (embedded second derivative) and
 // big (fields of 4 GiB and more); tilew: elements of one wave's LDS tile.
 struct BiasLaunch {
