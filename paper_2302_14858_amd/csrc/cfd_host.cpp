@@ -131,7 +131,7 @@ struct cfd_plan {
     bool bconcurrent = false;             // the biased kernel classes on forked streams
     int cus = 256;
     size_t max_lds = 65536;
-    bool xcd_interleave_ok = false;       // dispatch check passed: the XCD-interleaved per-item order covers every item
+    bool xcd_interleave_ok = false;       // dispatch check passed: the XCD-interleaved per-item order keeps a queue on one XCD
     // hybrid closure iteration: iterations (0: off), end-node offset c, lattice
     int iter_n = 0, iter_c = 2, lat[3] = {0, 0, 0};
     std::vector<Scheme> base_schemes;     // the block-closure schemes while schemes holds the iterated ones
@@ -481,10 +481,10 @@ cfd_status build_dense(cfd_plan *p);
 
 // Does this device deal a launch's workgroups round-robin over its kXCDq
 // XCDs, so that every aligned group of kXCDq consecutive workgroups runs on
-// kXCDq distinct XCDs?  The XCD-interleaved per-item order (each workgroup
-// takes the item of its group that belongs to the XCD it runs on) covers every
-// item only then.  Checked once per device on probe launches of several grid
-// sizes (the first XCD of a launch varies), the result cached.
+// kXCDq distinct XCDs?  The XCD-interleaved per-item order keeps a block-field
+// on one XCD only then (a matter of speed: every item is computed either way).
+// Checked once per device on probe launches of several grid sizes (the first
+// XCD of a launch varies), the result cached.
 bool xcd_dispatch_ok(int device) {
     static std::mutex mu;
     static std::map<int, bool> known;
@@ -960,8 +960,6 @@ cfd_status build_groups(cfd_plan *p) {
                         items.push_back(r < q[k].size() ? q[k][r] : WorkItem{-1, 0, 0, 0});
                 g.nitems = (int64_t)(items.size() - g.item0);
                 g.grid_persist = (int)std::min<int64_t>(g.nitems, (int64_t)nb * p->cus);
-                g.qoff_index = (int)qoffs.size();   // marker: workgroups pick their XCD's item
-                qoffs.push_back(-1);
             }
         } else {
             items.insert(items.end(), gitems[gi].begin(), gitems[gi].end());
