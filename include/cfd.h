@@ -267,9 +267,9 @@ typedef struct {
  * along i (edge ghosts are read), so the outer one has its ghost values.  The
  * plan computes the inner derivatives into a scratch buffer it owns (per
  * block-field and inner direction, the block extended along the outer
- * directions the plan pairs it with; the operators of a plan share them).
- * On a block both orders are the tensor product of the two line operators, so
- * their mean is either of them, and one is computed.
+ * directions the plan pairs it with; the operators of a plan share them);
+ * the first order's outer derivative stores half its value into the output
+ * and the second order's adds half of its own.
  * aux_field: for a U_M scheme ("(1)UM-" etc., Tab. ucd_slow), which samples
  * f'' as data, the field holding the second derivative of `field` along dir
  * (read on the interior nodes; field must be a single index); -1 for every

@@ -261,18 +261,22 @@ struct PassHost {
     int op[2] = {0, 0};   // plan op indices (output order)
     int sch[2] = {0, 0};  // scheme indices
     int N = 0, ng = 0, periodic = 0, nl = 0, par = 0, mi = 0, hw = 0;
-    int ext = 0;          // kernel extension: 1 iterated closures (end-value terms), 2 stage epilogue
+    int ext = 0;          // kernel extension: 1 iterated closures (end-value terms), 2 stage epilogue,
+                          // 3 accumulate into the output
     int P = 0, L = 0, lcode = 0;
     int C = 1;            // x lines: column chunks the LDS tile is staged in (divides P)
     const LineClass *cls = nullptr;
     // Passes of the symmetrised mixed derivatives read or write the plan's
     // scratch buffer: iomode 0 input -> output, 1 input -> scratch (first
-    // stage), 5 scratch -> output (second stage).  Their strides and offsets are
-    // set explicitly (geom) instead of from the block.
+    // stage), 5 scratch -> output (second stage), 6 scratch -> output
+    // accumulating (third stage, ext 3).  Their strides and offsets are set
+    // explicitly (geom) instead of from the block, and hscale multiplies their
+    // h^-d.
     // Passes of the fused wave stage: iomode 3 (first launch) and 4 (second
     // launch, after the first), run only by that stage.
     int iomode = 0;
     bool custom = false;
+    double hscale = 1.0;
     PassDesc geom{};
 };
 

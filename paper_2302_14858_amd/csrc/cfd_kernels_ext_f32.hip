@@ -1,5 +1,5 @@
 // FP32 instantiations of the line-kernel classes with a kernel extension
-// (iterated closures, Runge-Kutta stage epilogue; see
+// (iterated closures, Runge-Kutta stage epilogue, accumulating store; see
 // cfd_lines.h), compiled on their own so the build runs them in parallel.
 #include <hip/hip_runtime.h>
 
