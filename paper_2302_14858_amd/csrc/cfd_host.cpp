@@ -1257,73 +1257,42 @@ cfd_status build_biased(cfd_plan *p) {
     // block-field are adjacent, every direction's lines after each other, so
     // they share its input in the L2, and the fields of a block follow one
     // another, so they share the velocity.  Where the device deals workgroups
-    // round-robin over its 8 XCDs (each with an L2 of its own), (block, run of
-    // fields) units are dealt to XCD queues, largest first to the least loaded,
-    // and position 8 r + x holds queue x's r-th item (queues padded with empty
-    // items): a unit is at most 1/256 of the step (one field of the larger
-    // blocks), which balances the queues; the velocity comes from the last-level
-    // cache (64 blocks, 22 fields, X_2 pair, FP64: 454 us; units of 1/24 463).
-    const size_t nbops = bops.size();
+    // round-robin over its 8 XCDs (each with an L2 of its own), the class's work
+    // is dealt to XCD queues (bias_deal) and position 8 r + x holds queue x's
+    // r-th item (queues padded with empty items).
+    const size_t nbops = bops.size(), nblocks = p->blocks.size();
     using Key = std::array<int, 5>;
     auto key_of = [](const BiasLaunch &g) { return Key{g.sweep, g.hb, g.emb, g.big, g.wide}; };
-    struct Unit {
-        int b, f0, f1;
-        int64_t cost;
-    };
-    std::vector<Unit> units;
-    int64_t total = 0;
-    for (size_t b = 0; b < p->blocks.size(); ++b)
-        for (size_t i = 0; i < nbops; ++i)
-            total += pp[b * nbops + i].cost * (p->ops[bops[i]].field < 0 ? p->nfields : 1);
-    for (size_t b = 0; b < p->blocks.size(); ++b) {
-        Unit u{(int)b, 0, 0, 0};
-        for (int f = 0; f < p->nfields; ++f) {
-            int64_t c = 0;
-            for (size_t i = 0; i < nbops; ++i) {
-                const int of = p->ops[bops[i]].field;
-                if (of < 0 || of == f) c += pp[b * nbops + i].cost;
-            }
-            if (u.cost > 0 && u.cost + c > total / (32 * kXCDq)) {
-                units.push_back(u);
-                u = Unit{(int)b, f, f, 0};
-            }
-            u.cost += c;
-            u.f1 = f + 1;
-        }
-        if (u.cost > 0) units.push_back(u);
-    }
-    const bool deal = p->xcd_interleave_ok;
-    std::vector<int> queue(units.size(), 0);
-    if (deal) {
-        std::vector<size_t> ord(units.size());
-        for (size_t i = 0; i < ord.size(); ++i) ord[i] = i;
-        std::stable_sort(ord.begin(), ord.end(), [&](size_t x, size_t y) { return units[x].cost > units[y].cost; });
-        std::vector<int64_t> load(kXCDq, 0);
-        for (size_t i : ord) {
-            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-            queue[i] = k;
-            load[k] += units[i].cost;
-        }
+    auto selects = [&](const PassPlan &w, int f) { return p->ops[w.op].field < 0 || p->ops[w.op].field == f; };
+    std::map<Key, BiasLaunch> cls;
+    for (const PassPlan &w : pp) {
+        BiasLaunch &g = cls.emplace(key_of(w.g), w.g).first->second;
+        g.tilew = std::max(g.tilew, w.g.tilew);
     }
     std::map<Key, std::vector<std::vector<BiasItem>>> by_cls;
-    std::map<Key, BiasLaunch> cls;
-    for (size_t ui = 0; ui < units.size(); ++ui) {
-        const Unit &u = units[ui];
-        for (int f = u.f0; f < u.f1; ++f)
+    for (const auto &kc : cls) {
+        std::vector<std::vector<int64_t>> cost(nblocks, std::vector<int64_t>(p->nfields, 0));
+        for (size_t b = 0; b < nblocks; ++b)
             for (size_t i = 0; i < nbops; ++i) {
-                const size_t pi = u.b * nbops + i;
-                const PassPlan &w = pp[pi];
-                const int of = p->ops[w.op].field;
-                if (of >= 0 && of != f) continue;
-                const Key key = key_of(w.g);
-                auto &q = by_cls[key];
-                if (q.empty()) q.resize(kXCDq);
-                BiasLaunch &g = cls.emplace(key, w.g).first->second;
-                g.tilew = std::max(g.tilew, w.g.tilew);
-                for (int l0 = 0; l0 < bp[pi].nlines; l0 += w.step)
-                    q[w.g.sweep ? 0 : queue[ui]].push_back(BiasItem{(int)pi, f, l0, w.meta});
+                const PassPlan &w = pp[b * nbops + i];
+                if (key_of(w.g) != kc.first) continue;
+                for (int f = 0; f < p->nfields; ++f)
+                    if (selects(w, f)) cost[b][f] += w.cost;
             }
+        auto &q = by_cls[kc.first];
+        q.resize(kXCDq);
+        for (const BiasUnit &u : bias_deal(cost, kc.second.sweep ? 1 : kXCDq))   // sweep kernel: plain order
+            for (int f = u.f0; f < u.f1; ++f)
+                for (size_t i = 0; i < nbops; ++i) {
+                    const size_t pi = u.block * nbops + i;
+                    const PassPlan &w = pp[pi];
+                    if (key_of(w.g) != kc.first || !selects(w, f)) continue;
+                    const int64_t steps = (bp[pi].nlines + w.step - 1) / w.step;
+                    for (int64_t s = steps * u.part / u.parts; s < steps * (u.part + 1) / u.parts; ++s)
+                        q[u.queue].push_back(BiasItem{(int)pi, f, (int)(s * w.step), w.meta});
+                }
     }
+    const bool deal = p->xcd_interleave_ok;
     std::vector<BiasItem> items;
     for (auto &kv : by_cls) {
         BiasLaunch g = cls.at(kv.first);

@@ -57,8 +57,37 @@ static void tiles() {
                         }
 }
 
+// Work dealt to the queues: every line of every field once, no queue above 1.3 times the mean.
+static void queues() {
+    unsigned rng = 12345;
+    auto next = [&](int n) { return (int)((rng = rng * 1664525u + 1013904223u) >> 8) % n; };
+    for (int rep = 0; rep < 3000; ++rep) {
+        const int nb = 1 + (rep % 3 == 0 ? 0 : next(12)), nf = 1 + next(rep % 2 ? 3 : 24);
+        std::vector<std::vector<int64_t>> cost(nb, std::vector<int64_t>(nf));
+        int64_t total = 0;
+        for (auto &b : cost) {
+            const int64_t n = 4096 + next(2000000);
+            for (int64_t &c : b) total += c = n * next(4);   // operators that select some fields only
+        }
+        const std::vector<BiasUnit> units = bias_deal(cost, 8);
+        std::vector<int64_t> load(8, 0);
+        std::vector<std::vector<double>> seen(nb, std::vector<double>(nf, 0.0));
+        for (const BiasUnit &u : units) {
+            EXPECT(u.queue >= 0 && u.queue < 8 && u.f0 < u.f1 && u.part >= 0 && u.part < u.parts);
+            EXPECT(u.parts == 1 || u.f1 == u.f0 + 1);
+            load[u.queue] += u.cost;
+            for (int f = u.f0; f < u.f1; ++f) seen[u.block][f] += 1.0 / u.parts;
+        }
+        for (int b = 0; b < nb; ++b)
+            for (int f = 0; f < nf; ++f)
+                EXPECT(cost[b][f] == 0 || (seen[b][f] > 0.999 && seen[b][f] < 1.001));
+        for (int64_t l : load) EXPECT(10 * 8 * l <= 13 * total);
+    }
+}
+
 int main() {
     tiles();
+    queues();
     std::printf("%s (%d failures)\n", g_fail ? "FAIL" : "OK", g_fail);
     return g_fail ? 1 : 0;
 }

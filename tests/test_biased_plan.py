@@ -1,5 +1,6 @@
 """Host-side rules of the biased schemes (csrc/cfd_biased_plan.h) on the CPU, under the sanitizers:
-the LDS tile the host allots covers every index the selected kernel instance uses."""
+the LDS tile the host allots covers every index the selected kernel instance uses, and the queues
+that its work is dealt to balance."""
 import os
 import shutil
 import subprocess
