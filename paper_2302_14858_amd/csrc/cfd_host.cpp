@@ -586,6 +586,8 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
         max_units = std::max(max_units, nunits);
         if (ps.dir == 0) max_x = std::max(max_x, ps.N);
     }
+    if (end_values_lds(p->dtype != CFD_F64, max_x) > p->max_lds)
+        return fail(CFD_EUNSUPPORTED, "hybrid iteration: x lines too long for the end-value kernel's LDS tile");
     const int nw = (int)(wspecs.size() / end_weight_spec_size());
     const size_t es = p->dtype == CFD_F64 ? 8 : 4;
     HIPCHK(dmalloc((void **)&p->d_iops.p, recs.size()));

@@ -365,6 +365,8 @@ void fill_end_weight_spec(void *dst, int N, int c, const Scheme &blk, const Sche
 void fill_iter_op(void *dst, int pass, int o, int nbr_m, int nbr_p, int64_t ubase, int nunits, int N, int c, int Npad,
                   int64_t wofs, int64_t gofs, double hinv);
 hipError_t launch_end_weights(int ntab, const void *specs, double *data, double *scratch, int stride, hipStream_t st);
+// LDS of a workgroup of launch_end_values: the partial sums and the x tile
+size_t end_values_lds(int f32, int max_N);
 // ev0: receives the end values of iterate 1 (every line's iterate-0 end-node values, in its neighbours' slots);
 // max_N: the longest x line
 hipError_t launch_end_values(int f32, int nops, int max_units, int max_N, const void *ops, const PassDesc *passes,

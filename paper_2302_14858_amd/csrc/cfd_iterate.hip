@@ -281,10 +281,14 @@ hipError_t launch_end_weights(int ntab, const void *specs, double *data, double 
     return hipGetLastError();
 }
 
+size_t end_values_lds(int f32, int max_N) {
+    return (size_t)64 * (16 + ((max_N + 2 * kMaxHalf) | 1)) * (f32 ? 4 : 8);
+}
+
 hipError_t launch_end_values(int f32, int nops, int max_units, int max_N, const void *ops, const PassDesc *passes,
                              const double *weights, const void *in, void *ev0, void *endsf, hipStream_t st) {
     const dim3 grid((max_units + 63) / 64, nops);
-    const size_t lds = (size_t)64 * (16 + ((max_N + 2 * kMaxHalf) | 1)) * (f32 ? 4 : 8);
+    const size_t lds = end_values_lds(f32, max_N);
     if (f32)
         hipLaunchKernelGGL(k_end_values<float>, grid, dim3(256), lds, st, (const IterOp *)ops, passes, weights,
                            (const float *)in, (float *)ev0, (float *)endsf);
