@@ -2561,6 +2561,13 @@ cfd_status cfd_plan_get_schedule(const cfd_plan *p, int *persistent, int *split_
     std::map<std::pair<int, int>, int> used;
     for (const PassHost &ps : p->passes)
         if (!fused_pass(ps)) used[std::make_pair(ps.N, ps.dir == 0 ? 1 : 0)] = ps.P;
+    // the lines of W operators' embedded second derivatives, which set_schedule takes
+    // too (without effect: the biased kernel has a split of its own)
+    for (const PassHost &ps : p->emb_lines) {
+        const auto key = std::make_pair(ps.N, ps.dir == 0 ? 1 : 0);
+        auto it = p->sched_P.find(key);
+        used.emplace(key, it != p->sched_P.end() ? it->second : candidate_Ps(ps, p->dtype != CFD_F64, p->max_lds)[0]);
+    }
     if (n_classes) *n_classes = (int)used.size();
     int i = 0;
     for (auto &kv : used) {
