@@ -338,8 +338,10 @@ cfd_status cfd_plan_capture_graph(cfd_plan *p, const void *in_dev, void *out_dev
  * cfd_plan_graph_status). */
 cfd_status cfd_plan_launch_graph(cfd_plan *p, void *stream);
 
-/* How cfd_plan_launch_graph replays: 0 nothing captured, 1 an instantiated
- * HIP graph, 2 the eager fallback (the apply enqueued on each call). */
+/* How cfd_plan_launch_graph replays: 0 nothing captured, 1 the capture (an
+ * instantiated HIP graph, or the plain launches of a capture of at most four),
+ * 2 the eager fallback (the apply enqueued on each call, because it could not
+ * be captured). */
 cfd_status cfd_plan_graph_status(const cfd_plan *p, int *status);
 
 /* Count the non-finite values (NaN, +-inf) in the plan's output extent

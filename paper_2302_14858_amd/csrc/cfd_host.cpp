@@ -2210,28 +2210,30 @@ cfd_status cfd_plan_capture_graph(cfd_plan *p, const void *in_dev, void *out_dev
         return st;
     }
     if (e != hipSuccess) return fall_back();
-    p->graph = g;
-    e = hipGraphInstantiate(&p->gexec, g, nullptr, nullptr, 0);
-    if (e != hipSuccess) return fall_back();
     // A graph launch costs the host about 16 us whatever it holds, a plain launch
     // 1 - 2 us: a graph of up to kDirectNodes nodes is replayed as plain launches
     // on the captured buffers (one 16^3 block: 16.7 us per replay as a graph, 5.8
-    // as a launch).  Any change of the plan's launches drops the graph.
+    // as a launch) and not kept.  Any change of the plan's launches drops the capture.
     constexpr size_t kDirectNodes = 4;
     size_t nodes = 0;
     if (hipGraphGetNodes(g, nullptr, &nodes) == hipSuccess && nodes <= kDirectNodes && !p->concurrent && !p->bconcurrent) {
+        (void)hipGraphDestroy(g);
         p->direct = true;
         p->eager_in = in_dev;
         p->eager_out = out_dev;
+        return CFD_OK;
     }
     (void)hipGetLastError();
+    p->graph = g;
+    e = hipGraphInstantiate(&p->gexec, g, nullptr, nullptr, 0);
+    if (e != hipSuccess) return fall_back();
     return CFD_OK;
 }
 
 cfd_status cfd_plan_launch_graph(cfd_plan *p, void *stream) {
     if (!p) return fail(CFD_EINVAL, "cfd_plan_launch_graph: null plan");
     HIPCHK(hipSetDevice(p->device));
-    if (!p->gexec || p->direct) {
+    if (!p->gexec) {
         if (p->eager_in) return enqueue(p, p->eager_in, p->eager_out, (hipStream_t)stream);
         return fail(CFD_EINVAL, "cfd_plan_launch_graph: no graph captured");
     }
@@ -2241,7 +2243,7 @@ cfd_status cfd_plan_launch_graph(cfd_plan *p, void *stream) {
 
 cfd_status cfd_plan_graph_status(const cfd_plan *p, int *status) {
     if (!p || !status) return fail(CFD_EINVAL, "cfd_plan_graph_status: null argument");
-    *status = p->gexec ? 1 : (p->eager_in ? 2 : 0);
+    *status = (p->gexec || p->direct) ? 1 : (p->eager_in ? 2 : 0);
     return CFD_OK;
 }
 
