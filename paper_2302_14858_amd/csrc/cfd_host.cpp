@@ -315,6 +315,7 @@ int partition_length(const PassHost &ps, bool f32, int P) {
 // allocation-free apply calls this too).
 int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
     int ok[4], Lok[4], n = 0;
+    bool short_only[4];
     const size_t es = f32 ? 4 : 8;
     for (int P = 1; P <= 8; P *= 2) {
         const int L = partition_length(ps, f32, P);
@@ -328,15 +329,20 @@ int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
         if (lds > max_lds) continue;
         ok[n] = P;
         Lok[n] = L;
+        short_only[n] = std::all_of(k->Ls, k->Ls + k->nL, [](int l) { return l <= 16; });
         ++n;
     }
-    // default preference: the fewest partitions of at most 16 rows (x lines 12,
-    // for the LDS tile), which the kernel classes without long partitions take:
-    // fewer registers, more waves per SIMD, and one launch where a plan's lines
-    // all have them (64 blocks of 22 fields, penta D1 + D2, FP64: 570 us; with
-    // 16 rows in x lines too 800, with up to 24 rows in y and z lines 722); then
-    // the rest, most partitions first
-    const int Lcap = ps.dir == 0 ? 12 : 16;
+    // default preference: x lines: the fewest partitions of at most 12 rows, for
+    // the LDS tile; y and z lines: of at most 16 rows where a kernel class without
+    // longer ones takes them: fewer registers, more waves per SIMD, and one launch
+    // where a plan's lines all have them (64 blocks of 22 fields, penta D1 + D2,
+    // FP64: 570 us; with 16 rows in x lines too 800, with up to 24 rows in y and z
+    // lines 722).  Else of at most 24 rows: shorter partitions only cost there
+    // (penta D1 on 64 blocks of 20^3, 5 fields, FP32: 29.8 us, with 24 rows 24.4).
+    // Then the rest, most partitions first.
+    bool compact = false;
+    for (int i = 0; i < n; ++i) compact = compact || (Lok[i] <= 16 && short_only[i]);
+    const int Lcap = ps.dir == 0 ? 12 : compact ? 16 : 24;
     int m = 0;
     for (int i = 0; i < n; ++i)
         if (Lok[i] <= Lcap) out[m++] = ok[i];
@@ -613,6 +619,51 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
     return CFD_OK;
 }
 
+// Is one workgroup per item in XCD-interleaved order the better default?  Two
+// conditions.  The queues balance: the launches' fullest queues together hold at
+// most 1.3 times the mean share (64 blocks of 22 fields, penta D1 + D2, FP32: 313
+// us against 423; the wave operators of one 192^3 block, whose fields are too
+// few for the 8 queues: 507 us in XCD order, 152 in plain order).  And a
+// block-field's input and outputs (the mean by cost) are at most 8 MB, twice an
+// XCD's L2: larger ones leave it before their other lines come (one block, 22
+// fields, tri D1, FP64: 56^3, 6.5 MB, 38.8 us against 44.1; 64^3, 9.5 MB, 50.5
+// against 48.3; D1 + D2 of 64^3, 15.8 MB, 97 against 81).
+bool xcd_order_pays(const cfd_plan *p, const std::vector<Group> &groups, const std::vector<std::vector<int>> &gbf,
+                    const std::vector<std::vector<int64_t>> &gcost, const std::vector<int> &bf_queue,
+                    const std::vector<int64_t> &bf_cost, int64_t total) {
+    if (total == 0) return false;
+    double fullest = 0;
+    for (size_t gi = 0; gi < groups.size(); ++gi) {
+        if (fused_iomode(groups[gi].iomode)) continue;
+        std::vector<int64_t> q(kXCDq, 0);
+        int64_t sum = 0;
+        for (size_t e = 0; e < gcost[gi].size(); ++e) {
+            q[bf_queue[gbf[gi][e]]] += gcost[gi][e];
+            sum += gcost[gi][e];
+        }
+        const bool dealt = gcost[gi].size() >= 8 * kXCDq;   // shorter launches keep the plain order
+        fullest += dealt ? (double)*std::max_element(q.begin(), q.end()) : (double)sum / kXCDq;
+    }
+    if (fullest * kXCDq > 1.3 * total) return false;
+    const double es = p->dtype == CFD_F64 ? 8 : 4;
+    double bytes = 0;
+    for (size_t b = 0; b < p->blocks.size(); ++b) {
+        const cfd_block &bl = p->blocks[b];
+        double in = 1, out = 1;
+        for (int d = 0; d < 3; ++d) {
+            in *= bl.n[d] + 2 * bl.ng;
+            out *= bl.n[d];
+        }
+        for (int f = 0; f < p->nfields; ++f) {
+            double mine = in;
+            for (size_t o = 0; o < p->ops.size(); ++o)
+                if (p->schemes[o].kind != 1 && (p->ops[o].field < 0 || p->ops[o].field == f)) mine += out;
+            bytes += mine * es * (double)bf_cost[b * p->nfields + f] / (double)total;
+        }
+    }
+    return bytes <= 8e6;
+}
+
 cfd_status build_groups(cfd_plan *p) {
     HIPCHK(hipSetDevice(p->device));
     p->drop_graph();
@@ -828,6 +879,7 @@ cfd_status build_groups(cfd_plan *p) {
     std::vector<std::vector<WorkItem>> gitems;
     std::vector<std::vector<int>> gbf;        // block-field of each item
     std::vector<std::vector<int64_t>> gcost;  // rows x lines of each item
+    std::vector<int> gnops;                   // operators per item
     std::vector<Group> groups;
     std::vector<std::vector<int>> by_block(p->blocks.size());
     for (size_t i = 0; i < p->passes.size(); ++i) by_block[p->passes[i].block].push_back((int)i);
@@ -864,6 +916,7 @@ cfd_status build_groups(cfd_plan *p) {
                     gitems.emplace_back();
                     gbf.emplace_back();
                     gcost.emplace_back();
+                    gnops.push_back(ps.nops);
                 } else {
                     gi = it->second;
                 }
@@ -912,20 +965,18 @@ cfd_status build_groups(cfd_plan *p) {
             bf_queue[bf] = k;
             load[k] += bf_cost[bf];
         }
-        // Default launch shape: one workgroup per item in XCD-interleaved order
-        // if no queue holds more than 1.3 times the mean, else in plain order,
-        // on the persistent grid if that leaves it at least a quarter of a second
-        // round (64 blocks of 22 fields, penta D1 + D2, FP32: 313 us against 423;
-        // the wave operators of one 192^3 block, whose fields are too few for
-        // the 8 queues: 507 us in XCD order, 163 with one workgroup per item in
-        // plain order, 152 on the persistent grid; four blocks of 13 - 61 nodes,
-        // 5 fields, 1.04 rounds: 29.5, 31.1 and 37.6 us).
-        if (p->auto_shape) p->xcd = *std::max_element(load.begin(), load.end()) * kXCDq * 10 <= total * 13;
+        if (p->auto_shape) p->xcd = xcd_order_pays(p, groups, gbf, gcost, bf_queue, bf_cost, total);
     }
+    // In plain order the default is the persistent grid, unless that leaves it
+    // less than a quarter of a second round: one workgroup per item is faster then
+    // for a single operator (one block, FP64: 72^3, 5 fields, tri D1, 1.19 rounds,
+    // 46.4 -> 40.3 us; 64^3, 6 fields, penta D1, 1.13 rounds, 18.8 -> 15.4).  Two
+    // operators in four waves gain up to 7 % or lose up to 12 % (D1 + D2 of 60^3, 6
+    // fields, 34.2 and 31.8; of 48^3, 11 fields, 19.8 and 22.3) and keep it.
     if (p->auto_shape && !p->xcd) {
         p->persistent = true;
         for (size_t gi = 0; gi < groups.size(); ++gi) {
-            if (fused_iomode(groups[gi].iomode)) continue;
+            if (fused_iomode(groups[gi].iomode) || (gnops[gi] > 1 && groups[gi].wg == 4)) continue;
             const int64_t grid = (int64_t)occupancy(groups[gi]) * p->cus, n = (int64_t)gitems[gi].size();
             if (n > grid && 4 * n < 5 * grid) p->persistent = false;
         }
