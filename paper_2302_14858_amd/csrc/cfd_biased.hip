@@ -120,15 +120,7 @@ __global__ __launch_bounds__(256) void k_biased(const BiasItem *__restrict__ ite
     const int u = line % ps.nu, v = line / ps.nu;
 
     BCoef<T, HB> q;
-    {
-        const T *rec = coefs + (int64_t)ps.tab * kBiasRec;
-        q.alpha = rec[0];
-        q.inv_det = rec[24];
-#pragma unroll
-        for (int m = -HB; m <= HB; ++m) q.a[m + HB] = rec[1 + kBiasHalf + m];
-#pragma unroll
-        for (int m = -HB; m <= HB + 1; ++m) q.c[m + HB] = rec[12 + kBiasHalf + m];
-    }
+    load_coef(q, coefs + (int64_t)ps.tab * kBiasRec);
     const int N = ps.N;
     BLine<T> L{in + ps.in_base + (int64_t)item.field * ps.in_fstride + (int64_t)u * ps.su + (int64_t)v * ps.sv,
                ps.sd, N, ps.ng, ps.periodic};

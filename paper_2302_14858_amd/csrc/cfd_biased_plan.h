@@ -18,6 +18,9 @@ namespace cfd {
 
 // x lines of a wave are moved in at most this many passes of 64 lanes.
 constexpr int kRowPass = 16;
+// Rows of a lane's partition, at most, and log2 of a line's partitions.
+constexpr int kBiasMaxL = 12, kBiasMaxLgP = 6;
+static_assert((kBiasMaxL << kBiasMaxLgP) <= kBiasMaxPow, "the power tables cover the wave kernel's lines");
 
 // The fewest partitions of at most 12 rows, the rows spread evenly (L or L - 1
 // per partition): fewer partitions keep the stencil halo's share of the loads
@@ -30,9 +33,9 @@ constexpr int kRowPass = 16;
 // kRowPass passes or fewer.  False: the sweep kernel takes the lines.
 inline bool bias_split(int N, int dir, int emb, BiasSplit &s) {
     if (N < 2) return false;
-    for (int lg = 0; lg <= (dir == 0 || emb ? 6 : 4); ++lg) {
+    for (int lg = 0; lg <= (dir == 0 || emb ? kBiasMaxLgP : 4); ++lg) {
         const int L = (N + (1 << lg) - 1) >> lg;
-        if (L > 12) continue;
+        if (L > kBiasMaxL) continue;
         if (dir == 0) {
             const int Tn = N + 2 * (kBiasHalf + 1);   // at most
             const int rows = 64 >> lg, per = Tn > 32 ? 1 : Tn > 16 ? 2 : 4;

@@ -224,7 +224,7 @@ __device__ __forceinline__ void load_rows(const T *src, T (&val)[kRowPass], cons
     const char *sb = (const char *)src;
     constexpr uint32_t es = sizeof(T);
     const uint32_t gap = (uint32_t)(ps.sv - ps.nu * ps.su);   // from a plane's last row to the next plane's first
-    if (m.whole && m.nval <= ps.nu) {   // at most two planes
+    if (m.whole) {   // at most two planes
         const int cross = ps.nu - u0 - m.sub;   // this lane's rows from here on lie in the second
         m.each((uint32_t)ps.su * es, es, [&](int i, int r, uint32_t at) {
             val[i] = *(const T *)(sb + (at + (r >= cross ? gap * es : 0u)));

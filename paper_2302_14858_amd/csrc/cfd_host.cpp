@@ -1150,9 +1150,11 @@ cfd_status build_dense(cfd_plan *p) {
 }
 
 // Biased (upwind) operators: one BiasPass per (block, operator) over the
-// fields the operator selects, work items of 64 lines per (pass, field),
-// grouped by stencil half-width class; coefficient records in the plan's
-// element type.  Independent of the schedule, built once at plan creation.
+// fields the operator selects, work items of four waves' lines per (pass,
+// field) (64 lines in the sweep kernel), one launch per kernel class (stencil
+// half-width, embedded second derivative, row moves, offset width); coefficient
+// records in the plan's element type.  Independent of the schedule, built once
+// at plan creation.
 cfd_status build_biased(cfd_plan *p) {
     const bool f32 = p->dtype != CFD_F64;
     std::vector<int> bops;

@@ -142,17 +142,17 @@ struct PassDesc {
 
 // Biased (upwind) operator on the lines of one block along one direction
 // (cfd_biased.hip).  mode: -1 left-biased, +1 right-biased, 0 upwind by the
-// sign of the velocity field at vel_base, 2 the mean of both biases.  Coefficient record per table
-// (elements of the plan's type): [0] alpha, [1, 12) ba_{-5..5},
-// [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [27] -1 / alpha (0 for alpha =
-// 0), [kBiasPow + n] (-alpha)^n for
-// n = 0..kBiasMaxPow; W schemes also [25] beta of the embedded second
+// sign of the velocity field at vel_base, 2 the mean of both biases.
+// Coefficient record per table (elements of the plan's type): [0] alpha,
+// [1, 12) ba_{-5..5}, [12, 24) bc_{-5..6}, [24] 1 / (1 - alpha^2), [27]
+// -1 / alpha (0 for alpha = 0), [kBiasPow + n] (-alpha)^n for n =
+// 0..kBiasMaxPow; W schemes also [25] beta of the embedded second
 // derivative's system [a2, 1, a2] = (a2 / beta)(1 + beta S-)(1 + beta S+),
 // [28] -1 / beta, [kBiasSt2, + 11) its stencil times ba2 beta / a2,
 // [kBiasCl2, + 11) its left closure stencil times ba2 (both centred, unit
 // spacing; the right closure is the mirror image) and [kBiasPow2 + n] (-beta)^n.
 constexpr int kBiasSt2 = 32, kBiasCl2 = 48;
-constexpr int kBiasPow = 64, kBiasMaxPow = 1024;   // longest line of the wave kernel
+constexpr int kBiasPow = 64, kBiasMaxPow = 768;   // longest line of the wave kernel (bias_split)
 constexpr int kBiasPow2 = kBiasPow + kBiasMaxPow + 8;
 constexpr int kBiasRec = kBiasPow2 + kBiasMaxPow + 8;
 constexpr int kBiasIterN = 64;   // longest line of iterated biased closures
