@@ -124,6 +124,7 @@ struct cfd_plan {
     int64_t in_elems = 0, out_elems = 0;
     std::vector<PassHost> passes;
     std::map<std::pair<int, int>, int> sched_P;   // (N, x-direction) -> partitions per line
+    bool auto_parts = true;               // partitions without an entry in sched_P by build_groups' rule, until tuned
     bool auto_shape = true;               // launch shape by build_groups' rule, until a schedule is set or tuned
     bool persistent = true;
     bool split_x = false;                 // x-lines in a launch of their own
@@ -313,7 +314,7 @@ int partition_length(const PassHost &ps, bool f32, int P) {
 // how many.  A candidate needs a compiled class with a fitting L, and (x
 // lines) an LDS tile that fits next to the exchange area.  No heap use (the
 // allocation-free apply calls this too).
-int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
+int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4], bool longer) {
     int ok[4], Lok[4], n = 0;
     bool short_only[4];
     const size_t es = f32 ? 4 : 8;
@@ -339,10 +340,11 @@ int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
     // FP64: 570 us; with 16 rows in x lines too 800, with up to 24 rows in y and z
     // lines 722).  Else of at most 24 rows: shorter partitions only cost there
     // (penta D1 on 64 blocks of 20^3, 5 fields, FP32: 29.8 us, with 24 rows 24.4).
-    // Then the rest, most partitions first.
+    // Longer: x lines up to 16 rows, y and z lines up to 24.  Then the rest, most
+    // partitions first.
     bool compact = false;
     for (int i = 0; i < n; ++i) compact = compact || (Lok[i] <= 16 && short_only[i]);
-    const int Lcap = ps.dir == 0 ? 12 : compact ? 16 : 24;
+    const int Lcap = ps.dir == 0 ? (longer ? 16 : 12) : (compact && !longer ? 16 : 24);
     int m = 0;
     for (int i = 0; i < n; ++i)
         if (Lok[i] <= Lcap) out[m++] = ok[i];
@@ -351,9 +353,9 @@ int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]) {
     return m;
 }
 
-std::vector<int> candidate_Ps(const PassHost &ps, bool f32, size_t max_lds) {
+std::vector<int> candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, bool longer = false) {
     int c[4];
-    const int n = candidate_Ps(ps, f32, max_lds, c);
+    const int n = candidate_Ps(ps, f32, max_lds, c, longer);
     return std::vector<int>(c, c + n);
 }
 
@@ -619,6 +621,30 @@ cfd_status build_iteration(cfd_plan *p, std::vector<PassDesc> &pd, const std::ve
     return CFD_OK;
 }
 
+// Workgroups of a kernel class that a CU holds.
+int class_occupancy(const void *fn, int wg, size_t lds) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kWave * wg, lds) != hipSuccess || nb < 1) nb = 1;
+    (void)hipGetLastError();
+    return nb;
+}
+
+// Deals block-fields to the XCD queues by the cost of all their passes, largest
+// first to the least loaded: the same way for every launch, so a block-field's
+// x, y and z lines, also in separate launches, share one XCD's L2.
+std::vector<int> deal_block_fields(const std::vector<int64_t> &cost) {
+    std::vector<int> queue(cost.size(), 0), ord;
+    for (size_t bf = 0; bf < cost.size(); ++bf)
+        if (cost[bf]) ord.push_back((int)bf);
+    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+    std::vector<int64_t> load(kXCDq, 0);
+    for (int bf : ord) {
+        queue[bf] = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        load[queue[bf]] += cost[bf];
+    }
+    return queue;
+}
+
 // Is one workgroup per item in XCD-interleaved order the better default?  Two
 // conditions.  The queues balance: the launches' fullest queues together hold at
 // most 1.3 times the mean share (64 blocks of 22 fields, penta D1 + D2, FP32: 313
@@ -664,37 +690,31 @@ bool xcd_order_pays(const cfd_plan *p, const std::vector<Group> &groups, const s
     return bytes <= 8e6;
 }
 
-cfd_status build_groups(cfd_plan *p) {
-    HIPCHK(hipSetDevice(p->device));
-    p->drop_graph();
-    if (p->passes.empty()) {   // only biased operators
-        p->groups.clear();
-        p->nitems = 0;
-        return CFD_OK;
-    }
-    if (p->dtype == CFD_MIXED_BF16) return build_dense(p);
+// Work items of one field of a pass.
+int64_t pass_items(const cfd_plan *p, const PassHost &ps) {
+    const cfd_block &b = p->blocks[ps.block];
+    const int64_t nlines = ps.custom ? ps.geom.nlines : (int64_t)b.n[ps.dir == 0 ? 1 : 0] * b.n[ps.dir == 2 ? 1 : 2];
+    const int per_item = kWave * (waves_for(ps.P) / ps.P);
+    return (nlines + per_item - 1) / per_item;
+}
+
+// Partitions (those set by a schedule, else the first candidate) and kernel
+// class of every pass of the plain apply and, where its classes exist, of the
+// fused wave stage.
+cfd_status place_passes(cfd_plan *p, bool longer) {
     const bool f32 = p->dtype != CFD_F64;
-    // 1. schedule and kernel class of every pass (the fused wave stage's passes
-    //    only where their kernel classes exist, and not with iterated closures)
-    p->wave_fused_ok = p->wave_fused && p->iter_n == 0;
+    p->wave_fused_ok = p->wave_fused && p->iter_n == 0;   // not with iterated closures
     for (PassHost &ps : p->passes) {
         if (fused_pass(ps)) {
             ps.cls = nullptr;
             if (!p->wave_fused_ok) continue;
-            std::vector<int> cands = candidate_Ps(ps, f32, p->max_lds);
-            if (cands.empty()) {
+        }
+        std::vector<int> cands = candidate_Ps(ps, f32, p->max_lds, longer);
+        if (cands.empty()) {
+            if (fused_pass(ps)) {
                 p->wave_fused_ok = false;
                 continue;
             }
-            int P = cands[0];
-            auto it = p->sched_P.find(std::make_pair(ps.N, ps.dir == 0 ? 1 : 0));
-            if (it != p->sched_P.end() && std::find(cands.begin(), cands.end(), it->second) != cands.end())
-                P = it->second;
-            place_pass(ps, f32, P);
-            continue;
-        }
-        std::vector<int> cands = candidate_Ps(ps, f32, p->max_lds);
-        if (cands.empty()) {
             char buf[200];
             std::snprintf(buf, sizeof buf,
                           "no compiled line kernel for N=%d nl=%d nops=%d (stencil half-width %d, direction %d)",
@@ -711,32 +731,106 @@ cfd_status build_groups(cfd_plan *p) {
     // several classes (their partition lengths apart, the same kernel) and all
     // their items are no more than 16 workgroups per CU, one class with every
     // length takes them in one launch (four blocks of 13 - 61 nodes, 5 fields,
-    // penta D1 + D2: 46 us in two launches, 36 in one; on 64 blocks of 22 fields the smaller classes'
-    // registers are worth more, 570 us against 722 with a second launch).
-    {
-        using Fam = std::tuple<int, int, int, int, int, int, int, int>;
-        auto fam_of = [](const PassHost &ps) {
-            const LineClass *k = ps.cls;
-            return Fam{k->nl, k->nops, k->par, k->mi, k->hw, k->ext, k->wg, ps.iomode};
-        };
-        std::map<Fam, std::pair<std::set<int>, int64_t>> fam;   // partition lengths, items
-        for (const PassHost &ps : p->passes) {
-            if (!ps.cls) continue;
-            auto &f = fam[fam_of(ps)];
-            f.first.insert(ps.L);
-            const cfd_block &b = p->blocks[ps.block];
-            const int64_t nlines = ps.custom ? ps.geom.nlines : (int64_t)b.n[ps.dir == 0 ? 1 : 0] * b.n[ps.dir == 2 ? 1 : 2];
-            const int per_item = kWave * (waves_for(ps.P) / ps.P);
-            f.second += (nlines + per_item - 1) / per_item * ps.nfield;
+    // penta D1 + D2: 46 us in two launches, 36 in one; on 64 blocks of 22 fields
+    // the smaller classes' registers are worth more, 570 us against 722 with a
+    // second launch).
+    using Fam = std::tuple<int, int, int, int, int, int, int, int>;
+    auto fam_of = [](const PassHost &ps) {
+        const LineClass *k = ps.cls;
+        return Fam{k->nl, k->nops, k->par, k->mi, k->hw, k->ext, k->wg, ps.iomode};
+    };
+    std::map<Fam, std::pair<std::set<int>, int64_t>> fam;   // partition lengths, items
+    for (const PassHost &ps : p->passes) {
+        if (!ps.cls) continue;
+        auto &f = fam[fam_of(ps)];
+        f.first.insert(ps.L);
+        f.second += pass_items(p, ps) * ps.nfield;
+    }
+    for (PassHost &ps : p->passes) {
+        if (!ps.cls) continue;
+        const auto &f = fam.at(fam_of(ps));
+        if (f.second > 16 * p->cus) continue;
+        const LineClass *k = find_common_class(f32, ps.cls, f.first);
+        if (!k || chunked(k) != chunked(ps.cls)) continue;
+        ps.cls = k;
+        ps.lcode = (int)(std::find(k->Ls, k->Ls + k->nL, ps.L) - k->Ls);
+    }
+    return CFD_OK;
+}
+
+// Rounds of workgroups that the plain apply takes in plain order and, if that
+// is balanced (else the same), in XCD order; 0 if it has several launches.
+std::array<int64_t, 2> apply_rounds(const cfd_plan *p) {
+    struct Launch {
+        int wg = 0;
+        size_t lds = 0;
+        std::vector<int64_t> items;   // of each block-field
+    };
+    std::map<std::pair<const void *, int>, Launch> launches;   // one per kernel class and stage
+    const size_t nbf = p->blocks.size() * p->nfields;
+    std::vector<int64_t> cost(nbf, 0);
+    int64_t total = 0;
+    for (const PassHost &ps : p->passes) {
+        if (fused_pass(ps)) continue;
+        Launch &l = launches[std::make_pair(ps.cls->fn, ps.iomode)];
+        if (l.items.empty()) l.items.resize(nbf);
+        l.wg = ps.cls->wg;
+        l.lds = std::max(l.lds, pass_lds(ps, p->dtype != CFD_F64));
+        const int64_t n = pass_items(p, ps), c = n * kWave * waves_for(ps.P) * ps.L;
+        for (int f = ps.field0; f < ps.field0 + ps.nfield; ++f) {
+            l.items[(size_t)ps.block * p->nfields + f] += n;
+            cost[(size_t)ps.block * p->nfields + f] += c;
+            total += c;
         }
-        for (PassHost &ps : p->passes) {
-            if (!ps.cls) continue;
-            const auto &f = fam.at(fam_of(ps));
-            if (f.second > 16 * p->cus) continue;
-            const LineClass *k = find_common_class(f32, ps.cls, f.first);
-            if (!k || chunked(k) != chunked(ps.cls)) continue;
-            ps.cls = k;
-            ps.lcode = (int)(std::find(k->Ls, k->Ls + k->nL, ps.L) - k->Ls);
+    }
+    if (launches.size() != 1) return {0, 0};
+    const Launch &l = launches.begin()->second;
+    const std::vector<int> queue = deal_block_fields(cost);
+    std::vector<int64_t> load(kXCDq, 0), n(kXCDq, 0);
+    int64_t all = 0;
+    for (size_t bf = 0; bf < nbf; ++bf) {
+        load[queue[bf]] += cost[bf];
+        n[queue[bf]] += l.items[bf];
+        all += l.items[bf];
+    }
+    const bool balanced = *std::max_element(load.begin(), load.end()) * kXCDq * 10 <= total * 13;
+    const int64_t grid = (int64_t)class_occupancy(launches.begin()->first.first, l.wg, l.lds) * p->cus;
+    return {(all + grid - 1) / grid,
+            ((balanced ? *std::max_element(n.begin(), n.end()) * kXCDq : all) + grid - 1) / grid};
+}
+
+cfd_status build_groups(cfd_plan *p) {
+    HIPCHK(hipSetDevice(p->device));
+    p->drop_graph();
+    if (p->passes.empty()) {   // only biased operators
+        p->groups.clear();
+        p->nitems = 0;
+        return CFD_OK;
+    }
+    if (p->dtype == CFD_MIXED_BF16) return build_dense(p);
+    const bool f32 = p->dtype != CFD_F64;
+    // 1. partitions and kernel class of every pass.  One launch of at most three
+    //    rounds of workgroups takes the longer partitions, which make fewer
+    //    workgroups, where they save a round, or the round that the fullest XCD
+    //    queue adds to one: tri D1, FP64, 24 blocks of 24 - 48 nodes, one field,
+    //    20.8 us against 18.8; 8 blocks of 24 - 40, two fields, 14.9 and 11.4; the
+    //    RK4 step on 4^3 blocks of 17^3 150 and 142.  Where they save none they
+    //    lose: 27 blocks of 17^3 90 and 97; 20 blocks of 24 - 40, D1 + D2, 21.2 and
+    //    23.7; and the longer a plan the less a round is worth (64 blocks of 12 -
+    //    24, 5 fields, 4 rounds to 3, 26.7 and 27.3).  Plans of several launches
+    //    gain little or lose (dissipation and mixed derivatives of 40 x 35 x 13, 23
+    //    fields, FP32, 39.4 and 42.5).
+    cfd_status rp = place_passes(p, false);
+    if (rp != CFD_OK) return rp;
+    if (p->auto_parts) {
+        const std::array<int64_t, 2> compact = apply_rounds(p);
+        if (compact[1] > 1 && compact[0] <= 3) {
+            rp = place_passes(p, true);
+            if (rp != CFD_OK) return rp;
+            const std::array<int64_t, 2> longer = apply_rounds(p);
+            const bool fewer = longer[0] > 0 && (longer[0] < compact[0] || longer[1] == 1);
+            if (!fewer) rp = place_passes(p, false);
+            if (rp != CFD_OK) return rp;
         }
     }
     // 2. tables
@@ -931,20 +1025,12 @@ cfd_status build_groups(cfd_plan *p) {
             }
         }
     }
-    // XCD-aware modes: block-fields are dealt to kXCDq queues (least-loaded
-    // first, by the cost of all their passes in every group), the same way for
-    // every group, so a block-field's x, y and z lines, also in separate
-    // launches, share one XCD's L2.  Workgroup b runs on XCD b mod kXCDq.
+    // XCD-aware modes: block-fields are dealt to kXCDq queues by the cost of all
+    // their passes in every group.  Workgroup b runs on XCD b mod kXCDq.
     const int nbf = (int)(p->blocks.size() * p->nfields);
     std::vector<int> bf_queue(nbf, 0);
     if (p->auto_shape) p->persistent = p->split_x = p->concurrent = p->xcd = false;
-    auto occupancy = [](const Group &g) {   // workgroups per CU
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, g.fn, kWave * g.wg, g.lds) != hipSuccess || nb < 1)
-            nb = 1;
-        (void)hipGetLastError();
-        return nb;
-    };
+    auto occupancy = [](const Group &g) { return class_occupancy(g.fn, g.wg, g.lds); };
     if (p->xcd || (p->auto_shape && p->xcd_interleave_ok)) {
         std::vector<int64_t> bf_cost(nbf, 0);
         int64_t total = 0;
@@ -955,16 +1041,7 @@ cfd_status build_groups(cfd_plan *p) {
                 total += gcost[gi][e];
             }
         }
-        std::vector<int64_t> load(kXCDq, 0);
-        std::vector<int> ord;
-        for (int bf = 0; bf < nbf; ++bf)
-            if (bf_cost[bf]) ord.push_back(bf);
-        std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return bf_cost[x] > bf_cost[y]; });
-        for (int bf : ord) {
-            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-            bf_queue[bf] = k;
-            load[k] += bf_cost[bf];
-        }
+        bf_queue = deal_block_fields(bf_cost);
         if (p->auto_shape) p->xcd = xcd_order_pays(p, groups, gbf, gcost, bf_queue, bf_cost, total);
     }
     // In plain order the default is the persistent grid, unless that leaves it
@@ -2428,7 +2505,7 @@ cfd_status cfd_plan_autotune(cfd_plan *p, const void *in_dev, void *out_dev, voi
         p->persistent = bp;
         return r;
     }
-    p->auto_shape = false;
+    p->auto_shape = p->auto_parts = false;
     // one class per (line length, x or y/z, band, fused operators)
     std::map<std::tuple<int, int, int, int>, std::vector<int>> classes;
     for (const PassHost &ps : p->passes)

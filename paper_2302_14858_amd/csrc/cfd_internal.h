@@ -286,7 +286,7 @@ size_t x_tile_bytes(int P, int L, int hw, size_t es, int C = 1);
 bool chunked(const LineClass *k);
 int x_chunks(int P, int L, int hw, size_t es, size_t exch);
 int partition_length(const PassHost &ps, bool f32, int P);
-int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4]);
+int candidate_Ps(const PassHost &ps, bool f32, size_t max_lds, int out[4], bool longer = false);
 void fill_pass_desc(PassDesc &q, const cfd_block &b, int64_t in_off, const PassHost &ps, const int64_t out_base[2],
                     const int tab[2], const double hinv[2]);
 void place_pass(PassHost &ps, bool f32, int P);
