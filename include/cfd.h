@@ -357,10 +357,10 @@ cfd_status cfd_plan_count_nonfinite(cfd_plan *p, const void *out_dev, void *stre
 #define CFD_SCHED_XCD        4   /* block-fields dealt to the 8 XCDs, the same way in
                                     every launch, so the x/y/z passes of a block-field
                                     stay on one L2: a persistent grid walks one queue
-                                    per XCD; a per-item grid gets the items in an order
-                                    where each workgroup takes the item of its aligned
-                                    group of 8 that belongs to the XCD it runs on.  The
-                                    per-item form needs the device to deal workgroups
+                                    per XCD; a per-item grid gets its items in an order
+                                    where every eighth workgroup belongs to one queue.
+                                    The order decides the speed alone.  The per-item form
+                                    gains only if the device deals workgroups
                                     round-robin over 8 XCDs; plan creation checks that
                                     on probe launches and, if it does not hold,
                                     cfd_plan_set_schedule refuses the per-item form
