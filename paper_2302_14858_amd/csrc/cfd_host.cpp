@@ -819,10 +819,11 @@ cfd_status build_groups(cfd_plan *p) {
     //    23.7; and the longer a plan the less a round is worth (64 blocks of 12 -
     //    24, 5 fields, 4 rounds to 3, 26.7 and 27.3).  Plans of several launches
     //    gain little or lose (dissipation and mixed derivatives of 40 x 35 x 13, 23
-    //    fields, FP32, 39.4 and 42.5).
+    //    fields, FP32, 39.4 and 42.5).  A plan of one pass keeps the first choice,
+    //    which cfd_apply_block_noalloc takes and equals bit for bit.
     cfd_status rp = place_passes(p, false);
     if (rp != CFD_OK) return rp;
-    if (p->auto_parts) {
+    if (p->auto_parts && p->passes.size() > 1) {
         const std::array<int64_t, 2> compact = apply_rounds(p);
         if (compact[1] > 1 && compact[0] <= 3) {
             rp = place_passes(p, true);
